@@ -79,15 +79,11 @@ typedef struct {
     /* 1 = dense supernodal update blocks (a wide source panel updating several target
      * columns) run on the FP64 matrix cores (default); 0 = vector FMAs. */
     int32_t dense_mfma;
-    /* 1 = hybrid triangular solves (default): one launch per dependency level while levels
-     * are wide, and one persistent launch for the narrow levels at the top of the tree, in
-     * which blocks take work items in dependency order and wait, bounded, for the unknowns
-     * they read; items are assigned to blocks in a fixed order, which needs every block of
-     * the launch resident (a cooperative launch on a device the solve has to itself).
-     * 2 = the same with items taken from a ticket counter by the running blocks: slightly
-     * slower, but safe when other streams' work shares the device (the serving engine
-     * uses it).  0 = one launch per dependency level throughout.  All three give bitwise
-     * identical results. */
+    /* 1 = persistent triangular solves (default): one launch per triangle, in which running
+     * blocks take work items in dependency order from a ticket counter and wait, bounded, for
+     * the unknowns they read; an ordinary launch, safe when other streams' work shares the
+     * device.  2 = the same (accepted for callers that asked for ticket order by name).
+     * 0 = one launch per dependency level.  All give bitwise identical results. */
     int32_t persistent_solve;
     /* 1 = the refactorization's per-level launches (everything after the value update) are
      * recorded into a HIP graph at the first kkt_refactor after kkt_bind and replayed by
@@ -342,9 +338,8 @@ int kkt_batch_refactor(kkt_batch *b, const double *const *d_values, hipStream_t 
 /* kkt_refine of every handle of the batch with one right-hand side each: d_b, d_x host
  * arrays of count device pointers (FP64[n] of that handle), info host kkt_info[count] (may
  * be NULL).  Up to 8 handles are refined at once, each by a host thread on a stream of the
- * batch ordered after the caller's stream (which is why a batch's handles take their
- * persistent solve items by ticket, see persistent_solve = 2).  Waits.  Returns the first
- * error, else the worst warning. */
+ * batch ordered after the caller's stream.  Waits.  Returns the first error, else the worst
+ * warning. */
 int kkt_batch_refine(kkt_batch *b, const double *const *d_b, double *const *d_x, kkt_info *info,
                      hipStream_t stream);
 

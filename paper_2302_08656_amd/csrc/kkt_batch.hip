@@ -321,9 +321,6 @@ int kkt_batch_create(kkt_handle *const *handles, int32_t count, kkt_batch **out)
         }
         b->rstreams.push_back(st);
     }
-    // refinements of several handles run at once on those streams: their persistent solves
-    // take items by ticket (bitwise the same results as the fixed order)
-    for (auto *h : b->hs) h->tickets = true;
     {
         const hipError_t e = b->fp32 ? hipFuncSetAttribute(reinterpret_cast<const void *>(&k_batch_level<BigCfg<float>>),
                                                            hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -72,22 +72,24 @@ __device__ __forceinline__ void clear_status_body(DevStatus *st, unsigned long l
     for (int t = threadIdx.x; t < kCountSlots; t += blockDim.x) pcount[t] = 0;
 }
 
-// The per-call inputs of the recorded graphs (the values of A, the right-hand side): a
-// one-thread launch stores them before a replay and the recorded kernels read them here, so
-// one recording serves every call.
+// The per-call pointers of the recorded graphs (the values of A, the right-hand side, the
+// solution): a one-thread launch stores them before a replay and the recorded kernels read
+// them here, so one recording serves every call.
 struct CallPtrs {
     const double *v;
     const double *b;
+    double *x;
 };
 
 // stores the call's inputs and clears the status words and pivot counters of the call
 // (one block of 256 threads)
-__global__ __launch_bounds__(256) void k_set_call(CallPtrs *dst, const double *v, const double *b, DevStatus *st,
-                                                  unsigned long long *pcount) {
+__global__ __launch_bounds__(256) void k_set_call(CallPtrs *dst, const double *v, const double *b, double *x,
+                                                  DevStatus *st, unsigned long long *pcount) {
     clear_status_body(st, pcount);
     if (threadIdx.x == 0) {
         dst->v = v;
         dst->b = b;
+        dst->x = x;
     }
 }
 
@@ -95,6 +97,15 @@ __global__ __launch_bounds__(256) void k_set_call(CallPtrs *dst, const double *v
 __device__ __forceinline__ const double *call_ptr(const double *const *p) {
     return reinterpret_cast<const double *>(__hip_atomic_load(reinterpret_cast<const unsigned long long *>(p),
                                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+
+// the recorded call's solution vector, in scalar registers
+__device__ __forceinline__ double *call_x(const CallPtrs *call) {
+    const unsigned long long p = __hip_atomic_load(reinterpret_cast<const unsigned long long *>(&call->x),
+                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)p);
+    const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(p >> 32));
+    return reinterpret_cast<double *>((unsigned long long)hi << 32 | lo);
 }
 
 // Rows of the update passes taken by one group of 8 lanes: the group issues the loads of
@@ -1363,11 +1374,12 @@ struct SolveArgs {
     const double *bp;     // forward right-hand side r[P[i]] * b[P[i]] (permuted order)
     double *y;            // forward output / backward input (permuted)
     double *xt;           // backward output (permuted)
-    double *x;            // backward output (original order)
+    double *x;            // backward output (original order), null: the recorded call's
+    const CallPtrs *call;
     double *psum;         // forward: partial sums of the early L columns of helped rows
     double *usum;         // backward: partial sums of the early U columns of helped rows
     int *abort;           // persistent mode: raised by a wait that timed out
-    int *tick;            // persistent mode: next item to take (forward, backward)
+    int *tick;            // persistent mode: next item to take
 };
 
 constexpr unsigned long long kUnset = 0x7ff4dead0badf00dULL;   // signaling NaN
@@ -1644,7 +1656,7 @@ __device__ __forceinline__ void usolve_item(const SolveArgs<TF> &a, int item, do
     double dv = 1.0, yv = 0.0, ci = 0.0;
     int qi = 0;
     {
-        for (int e = tid; e < w * kPanelMax; e += kBlock) {
+        for (int e = tid; e < w * kPanelMax; e += blockDim.x) {
             const int r = e / kPanelMax, c = e % kPanelMax;
             const int d = a.rinfo[s + r].x;
             blk[r * kRowLd + c] = c > r && c < w ? (double)a.lucsr[d + (c - r)] : 0.0;
@@ -1690,73 +1702,64 @@ template <class TF>
 __global__ __launch_bounds__(256) void k_usolve_level(int item0, SolveArgs<TF> a) {
     __shared__ double ext[kPanelMax];
     __shared__ __align__(16) double blk[kPanelMax * kRowLd];
+    if (!a.x) a.x = call_x(a.call);
     usolve_item<false>(a, item0 + blockIdx.x, ext, blk);
 }
 
 // Persistent solves: the items of levels [i0, i1) in level order; an item only reads
-// unknowns of items of lower levels, i.e. of smaller index.  Two ways to hand out items:
-//  - fixed (kTicket = false): item i0 + k on block k % gridDim.x, each block in increasing
-//    order.  The unfinished item of smallest index can always proceed once its block runs,
-//    so the launch drains when every block is resident at once (a cooperative launch on a
-//    device the launch has to itself);
-//  - ticket (kTicket = true): running blocks take items from a counter (*tick, zeroed by
-//    k_solve_reset), each block in increasing order.  A block takes a ticket only while it
-//    runs and works through its tickets in order, so the unfinished item of smallest index
-//    is always held by a running block that is working on it: the launch drains on whatever
-//    share of the device it gets, with other streams' kernels beside it.  The next ticket
-//    is requested at the start of an item and read at its end, so the counter's round trip
-//    overlaps the item's loads; the counter still costs a round trip per item, which is why
-//    the fixed order is kept for a device that the solve has to itself.
+// unknowns of items of lower levels, i.e. of smaller index.  The blocks take items from a
+// counter (*tick, zeroed by the solve's set-up), each block in increasing order.  A block
+// takes a ticket only while it runs and works through its tickets in order, so the unfinished
+// item of smallest index is always held by a running block that is working on it: the launch
+// drains on whatever share of the device it gets, with other streams' kernels beside it, and
+// needs no cooperative launch.  (A fixed item order with every block resident needs one, and
+// cooperative launches run on a hardware queue of their own: they cost about 30 us of queue
+// switches around each launch, and once a process's streams hold four hardware queues, the
+// fifth slows every launch of the process by about 15 us: 1,075 instead of 430 us for a
+// 200-bus step with three handles alive.)
+// The next ticket is requested at the start of an item by a wavefront of its own (the fifth;
+// the items' rows fill four) and read at the item's end: a wavefront's loads return in order,
+// so on a wavefront with rows the counter's round trip would stand before the item's loads
+// (25,000 buses, two solved columns: 774 instead of 863 us; 70,000 buses: 24 us a step).
 // LDS of the persistent and fused forward loops: ext, ys, the ticket and the staged panel
 struct SolveLds {
     double ext[kPanelMax];
     double ys[kSolvePack];
-    int next;
-    int pad[3];
+    int next[2];
+    int pad[2];
     double blk[kPanelMax * kRowLd];
 };
 static_assert(offsetof(SolveLds, blk) % 16 == 0, "the staged panel is read in 16-byte pairs");
 
-// The ticket loop (blocks take items i0 + *tick++ in increasing order, see above) over the
-// forward (kFwd) or backward items [i0, i1).
+constexpr int kPersThreads = kBlock + 64;   // threads of the persistent solves' blocks
+
 template <bool kFwd, class TF>
-__device__ __forceinline__ void ticket_items(int i0, int i1, const SolveArgs<TF> &a, int *tick, SolveLds &L) {
-    if (threadIdx.x == 0) L.next = atomicAdd(tick, 1);
+__device__ __forceinline__ void persistent_items(int i0, int i1, const SolveArgs<TF> &a) {
+    __shared__ SolveLds L;
+    if (threadIdx.x == kBlock) L.next[0] = atomicAdd(a.tick, 1);
     __syncthreads();
-    int cur = L.next;
-    while (i0 + cur < i1) {
+    int cur = L.next[0];
+    for (int par = 1; i0 + cur < i1; par ^= 1) {
         int nt = 0;
-        if (threadIdx.x == 0) nt = atomicAdd(tick, 1);
+        if (threadIdx.x == kBlock) nt = atomicAdd(a.tick, 1);
         if constexpr (kFwd) lsolve_item<true>(a, i0 + cur, L.ext, L.blk, L.ys);
         else usolve_item<true>(a, i0 + cur, L.ext, L.blk);
-        __syncthreads();                     // every thread is done with the item and `next`
-        if (threadIdx.x == 0) L.next = nt;
+        // the slot was last read two barriers ago
+        if (threadIdx.x == kBlock) L.next[par] = nt;
         __syncthreads();
-        cur = L.next;
+        cur = L.next[par];
     }
 }
 
-template <bool kFwd, bool kTicket, class TF>
-__device__ __forceinline__ void persistent_items(int i0, int i1, const SolveArgs<TF> &a, int *tick) {
-    __shared__ SolveLds L;
-    if constexpr (!kTicket) {
-        for (int item = i0 + blockIdx.x; item < i1; item += gridDim.x) {
-            if constexpr (kFwd) lsolve_item<true>(a, item, L.ext, L.blk, L.ys);
-            else usolve_item<true>(a, item, L.ext, L.blk);
-        }
-        return;
-    }
-    ticket_items<kFwd>(i0, i1, a, tick, L);
+template <class TF>
+__global__ __launch_bounds__(kPersThreads) void k_lsolve_persistent(int i0, int i1, SolveArgs<TF> a) {
+    persistent_items<true>(i0, i1, a);
 }
 
-template <class TF, bool kTicket>
-__global__ __launch_bounds__(256) void k_lsolve_persistent(int i0, int i1, SolveArgs<TF> a) {
-    persistent_items<true, kTicket>(i0, i1, a, a.tick);
-}
-
-template <class TF, bool kTicket>
-__global__ __launch_bounds__(256) void k_usolve_persistent(int i0, int i1, SolveArgs<TF> a) {
-    persistent_items<false, kTicket>(i0, i1, a, a.tick + 1);
+template <class TF>
+__global__ __launch_bounds__(kPersThreads) void k_usolve_persistent(int i0, int i1, SolveArgs<TF> a) {
+    if (!a.x) a.x = call_x(a.call);
+    persistent_items<false>(i0, i1, a);
 }
 
 // Block blk of the f.nsolve extra blocks of a refactorization launch that run the items of
@@ -1951,12 +1954,16 @@ __global__ __launch_bounds__(256) void k_unpermute(int n, const int32_t *__restr
 // residual, sparse products and Krylov vector kernels (FP64)
 
 // res = b - A x (8 lanes per row, kRowsPerGroup rows per group, grid-stride) and block
-// maxima of |res|, |x|, |b| into part[3 * block + {0, 1, 2}]
+// maxima of |res|, |x|, |b| into part[3 * block + {0, 1, 2}]; v0, x0, b0 null: those of the
+// recorded call
 __global__ __launch_bounds__(256) void k_residual(int n, const int32_t *__restrict__ rowptr,
-                                                  const int32_t *__restrict__ col, const double *__restrict__ v,
-                                                  const double *__restrict__ x, const double *__restrict__ b,
+                                                  const int32_t *__restrict__ col, const double *v0,
+                                                  const double *x0, const double *b0, const CallPtrs *call,
                                                   double *__restrict__ res, double *__restrict__ part) {
     __shared__ double red[3][4];
+    const double *__restrict__ v = v0 ? v0 : call_ptr(&call->v);
+    const double *__restrict__ x = x0 ? x0 : call_x(call);
+    const double *__restrict__ b = b0 ? b0 : call_ptr(&call->b);
     const double qnan = __longlong_as_double(0x7ff8000000000000LL);
     double rn = 0.0, xn = 0.0, bn = 0.0;
     const int gl = threadIdx.x & 7;

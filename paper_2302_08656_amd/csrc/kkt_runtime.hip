@@ -36,7 +36,7 @@ struct Dev {
     DevStatus *st;
     ResNorms *rn;
     int *tick;          // ticket counters of the persistent solves (forward, backward, fused tail)
-    CallPtrs *call;     // the values and right-hand side of the current call (recorded graphs)
+    CallPtrs *call;     // values, right-hand side and solution of the current call (recorded graphs)
 };
 
 // most blocks of a refactor launch that run forward-solve items (kkt_refactor_refine; at 70k
@@ -86,10 +86,7 @@ struct kkt_handle {
     // bound to the library's static scratch array: nothing is allocated after the bind (no
     // graph is recorded; the level launches go one by one)
     bool on_scratch = false;
-    // the persistent solves take items by ticket (persistent_solve = 2, or a device without
-    // cooperative launches): safe when other streams share the device
-    bool tickets = false;
-    int grid_l = 1, grid_u = 1;  // co-resident blocks of the persistent solve kernels
+    int grid_l = 1, grid_u = 1;  // blocks of the persistent solve kernels that fill the device
     int ncu = 1;                 // compute units of the bound device
     // the refactorization's per-level launches, recorded once per bind on the capture stream
     // (created at the first bind) and replayed on the caller's stream
@@ -286,20 +283,8 @@ int upload(T *dst, const std::vector<T> &src, hipStream_t s) {
     return KKT_OK;
 }
 
-// x = Q C (L U)^-1 P R b for one column (both in original order)
-// One launch of a persistent solve kernel over items [i0, i1) with at most as many blocks
-// as the device holds at once: cooperative for the fixed item order (every block resident),
-// plain for the ticket order (progress does not need residency).
-template <class K, class A>
-hipError_t launch_persistent(K kernel, bool ticket, int grid, int i0, int i1, A &a, hipStream_t s) {
-    if (ticket) {
-        kernel<<<grid, kBlock, 0, s>>>(i0, i1, a);
-        return hipGetLastError();
-    }
-    void *args[] = {&i0, &i1, &a};
-    return hipLaunchCooperativeKernel(reinterpret_cast<const void *>(kernel), dim3(grid), dim3(kBlock), args, 0, s);
-}
-
+// x = Q C (L U)^-1 P R b for one column (both in original order); b and x null: those of the
+// recorded call.
 // forward = false: the forward part already ran (the fused refactorization), only the
 // backward part is enqueued
 template <class TF>
@@ -309,7 +294,7 @@ int enqueue_solve_t(kkt_handle *h, const double *b, double *x, hipStream_t s, bo
     const int n = h->sym.n;
     const bool pers = h->opts.persistent_solve != 0;
     SolveArgs<TF> a{d.l_item4, d.l_rows4, d.rinfo4, d.csr_col, d.Q, static_cast<const TF *>(d.lucsr), d.c, d.bp, d.y,
-                    d.xt, x, d.psum, d.usum, &d.st->abort, d.tick};
+                    d.xt, x, d.call, d.psum, d.usum, &d.st->abort, d.tick};
     if (forward)
         timed(h, KKT_PROF_LSOLVE, s, [&] {
             k_solve_reset<<<blocks_for(n, 256), 256, 0, s>>>(n, b, d.call, d.r, d.P, d.bp, d.y, d.xt, d.psum, d.usum,
@@ -322,32 +307,19 @@ int enqueue_solve_t(kkt_handle *h, const double *b, double *x, hipStream_t s, bo
         if (cnt) timed(h, KKT_PROF_LSOLVE, s, [&] { k_lsolve_level<TF><<<cnt, kBlock, 0, s>>>(g.l_lvl[l], a); });
     }
     const int li0 = g.l_lvl[lsplit], li1 = forward ? g.l_lvl.back() : li0;
-    if (li1 > li0) {
-        hipError_t e = hipSuccess;
+    if (li1 > li0)
         timed(h, KKT_PROF_LSOLVE, s,
-              [&] {
-                  const int gr = std::min(li1 - li0, h->grid_l);
-                  e = h->tickets ? launch_persistent(k_lsolve_persistent<TF, true>, true, gr, li0, li1, a, s)
-                                 : launch_persistent(k_lsolve_persistent<TF, false>, false, gr, li0, li1, a, s);
-              });
-        HIPCHK(e);
-    }
+              [&] { k_lsolve_persistent<TF><<<std::min(li1 - li0, h->grid_l), kPersThreads, 0, s>>>(li0, li1, a); });
     // backward: the persistent launch for levels below u_split, then level launches
     a.item = d.u_item4;
     a.rows = d.u_rows4;
     a.rinfo = d.urinfo4;
+    a.tick = d.tick + 1;
     const int usplit = pers ? g.u_split : 0;
     const int ui1 = g.u_lvl[usplit];
-    if (ui1 > 0) {
-        hipError_t e = hipSuccess;
+    if (ui1 > 0)
         timed(h, KKT_PROF_USOLVE, s,
-              [&] {
-                  const int gr = std::min(ui1, h->grid_u);
-                  e = h->tickets ? launch_persistent(k_usolve_persistent<TF, true>, true, gr, 0, ui1, a, s)
-                                 : launch_persistent(k_usolve_persistent<TF, false>, false, gr, 0, ui1, a, s);
-              });
-        HIPCHK(e);
-    }
+              [&] { k_usolve_persistent<TF><<<std::min(ui1, h->grid_u), kPersThreads, 0, s>>>(0, ui1, a); });
     for (size_t l = usplit; l + 1 < g.u_lvl.size(); ++l) {
         const int cnt = g.u_lvl[l + 1] - g.u_lvl[l];
         if (cnt) timed(h, KKT_PROF_USOLVE, s, [&] { k_usolve_level<TF><<<cnt, kBlock, 0, s>>>(g.u_lvl[l], a); });
@@ -360,10 +332,10 @@ int enqueue_solve(kkt_handle *h, const double *b, double *x, hipStream_t s, bool
     return by_precision(h, [&](auto tag) { return enqueue_solve_t<decltype(tag)>(h, b, x, s, forward); });
 }
 
-// stores the call's values (and right-hand side, or null) for the recorded kernels and
-// clears the status words (before anything of the call can raise a flag)
-int set_call(kkt_handle *h, const double *v, const double *b, hipStream_t s) {
-    timed(h, KKT_PROF_UPDATE, s, [&] { k_set_call<<<1, 256, 0, s>>>(h->d.call, v, b, h->d.st, h->d.pcount); });
+// stores the call's values (and right-hand side and solution, or null) for the recorded
+// kernels and clears the status words (before anything of the call can raise a flag)
+int set_call(kkt_handle *h, const double *v, const double *b, double *x, hipStream_t s) {
+    timed(h, KKT_PROF_UPDATE, s, [&] { k_set_call<<<1, 256, 0, s>>>(h->d.call, v, b, x, h->d.st, h->d.pcount); });
     HIPCHK(hipGetLastError());
     return KKT_OK;
 }
@@ -450,7 +422,7 @@ int enqueue_levels_t(kkt_handle *h, hipStream_t s, bool fused) {
     const int u0 = g.copy_uat[0], nup = (int)g.copy_k.size() - u0, ntop = nlev - g.copy_lvl;
     int ucopied = u0, ktop = 0;
     const SolveArgs<T> fs{d.l_item4, d.l_rows4, d.rinfo4, d.csr_col, d.Q, static_cast<const T *>(d.lucsr), d.c,
-                          d.bp, d.y, d.xt, nullptr, d.psum, d.usum, &d.st->abort, d.tick + 2};
+                          d.bp, d.y, d.xt, nullptr, d.call, d.psum, d.usum, &d.st->abort, d.tick + 2};
     const int nfl = (int)g.l_lvl.size() - 1;
     {
         // fused: the column pass also sets up the solve (bp from the stored right-hand side,
@@ -543,7 +515,7 @@ int enqueue_levels_t(kkt_handle *h, hipStream_t s, bool fused) {
     if (fused && solved < nfl) {
         const int j0 = g.l_lvl[solved], j1 = g.l_lvl[nfl];
         timed(h, KKT_PROF_LSOLVE, s, [&] {
-            k_lsolve_persistent<T, true><<<std::min(j1 - j0, h->grid_l), kBlock, 0, s>>>(j0, j1, fs);
+            k_lsolve_persistent<T><<<std::min(j1 - j0, h->grid_l), kPersThreads, 0, s>>>(j0, j1, fs);
         });
     }
     if (!copy_rest_left)
@@ -564,16 +536,23 @@ void enqueue_dots(kkt_handle *h, int nv, const double *V, const double *w, doubl
     timed(h, KKT_PROF_KRYLOV, s, [&] { k_reduce_parts<<<nv, 256, 0, s>>>(nv, kDotBlocks, h->d.part, dst, accumulate); });
 }
 
-// infinity norms of b - A x into the status block; returns berr on the host (and the
-// status block read with it in *sto)
-int residual_berr(kkt_handle *h, const double *x, const double *b, double *berr, double *den, hipStream_t s,
-                  DevStatus *sto = nullptr) {
+// infinity norms of b - A x, x and b into the status block (v, x, b null: those of the
+// recorded call)
+int enqueue_residual(kkt_handle *h, const double *v, const double *x, const double *b, hipStream_t s) {
     const Dev &d = h->d;
-    const int n = h->sym.n;
+    const int n = h->sym.n, nb = norm_blocks(n);
     timed(h, KKT_PROF_RESIDUAL, s, [&] {
-        k_residual<<<kNormBlocks, 256, 0, s>>>(n, d.a_rowptr, d.a_colind, h->d_values, x, b, d.res, d.part);
+        k_residual<<<nb, 256, 0, s>>>(n, d.a_rowptr, d.a_colind, v, x, b, d.call, d.res, d.part);
     });
-    timed(h, KKT_PROF_RESIDUAL, s, [&] { k_max_parts<<<1, 256, 0, s>>>(kNormBlocks, 3, d.part, &d.rn->rnorm); });
+    timed(h, KKT_PROF_RESIDUAL, s, [&] { k_max_parts<<<1, 256, 0, s>>>(nb, 3, d.part, &d.rn->rnorm); });
+    HIPCHK(hipGetLastError());
+    return KKT_OK;
+}
+
+// berr on the host from the norms of enqueue_residual (and the status block read with them
+// in *sto)
+int residual_berr(kkt_handle *h, double *berr, double *den, hipStream_t s, DevStatus *sto = nullptr) {
+    const Dev &d = h->d;
     // the residual norms are carved right after the status block: one read-back takes both
     const size_t off = static_cast<size_t>(reinterpret_cast<const char *>(d.rn) - reinterpret_cast<const char *>(d.st));
     if (off < sizeof(DevStatus) || off + sizeof(ResNorms) > sizeof(h->h_stage)) return KKT_ERR_DEVICE;
@@ -589,6 +568,16 @@ int residual_berr(kkt_handle *h, const double *x, const double *b, double *berr,
     if (*den == 0.0) *berr = rn.rnorm == 0.0 ? 0.0 : INFINITY;
     else *berr = rn.rnorm / *den;
     return KKT_OK;
+}
+
+// One step of Algorithm 1 for the recorded call: value update, refactorization with the
+// forward substitution riding in it, backward substitution, residual.  Everything is one
+// chain of launches on one queue.
+int enqueue_step(kkt_handle *h, hipStream_t s) {
+    int rc = enqueue_levels(h, s, true);
+    if (!rc) rc = enqueue_solve(h, nullptr, nullptr, s, false);
+    if (!rc) rc = enqueue_residual(h, nullptr, nullptr, nullptr, s);
+    return rc;
 }
 
 // Approximate preconditioner application: `sweeps` sweeps per triangle, each triangle from
@@ -634,26 +623,27 @@ int enqueue_approx_solve(kkt_handle *h, const double *b, double *x, int sweeps, 
     return by_precision(h, [&](auto tag) { return enqueue_approx_solve_t<decltype(tag)>(h, b, x, sweeps, s); });
 }
 
-// FGMRES on one column from the first solve x = M^-1 b.  fused: the refactorization and the
-// forward part of that solve were enqueued together; the backward part is enqueued here and
-// the factorization's status is checked with the first residual (a failed factorization
-// returns its error with info = {0, error, inf, perturbed pivots}, as kkt_refine does).
+// FGMRES on one column from the first solve x = M^-1 b.  fused: the refactorization, that
+// solve and its residual were enqueued together; the factorization's status is checked with
+// the first residual (a failed factorization returns its error with info = {0, error, inf,
+// perturbed pivots}, as kkt_refine does).
 int fgmres_column(kkt_handle *h, const double *b, double *x, kkt_info *info, hipStream_t s, bool fused = false) {
     const Dev &d = h->d;
     const int n = h->sym.n;
     const int m = h->opts.gmres_restart;
     const double tol = h->opts.berr_tol;
-    int rc = enqueue_solve(h, b, x, s, !fused);
+    int rc = fused ? KKT_OK : enqueue_solve(h, b, x, s);
     if (rc) return rc;
     int64_t pert = 0;
-    std::vector<double> H((size_t)(m + 1) * m, 0.0), cs(m), sn(m), gv(m + 1), yv(m);
+    std::vector<double> H, cs(m), sn(m), gv(m + 1), yv(m);   // H: made by the first Arnoldi step
     int it = 0;
     double berr = 0.0, den = 0.0;
     int status = KKT_OK;
     const unsigned nb = blocks_for(n, 256);
     for (bool first = true;; first = false) {
         DevStatus st{};
-        rc = residual_berr(h, x, b, &berr, &den, s, &st);
+        rc = fused && first ? KKT_OK : enqueue_residual(h, h->d_values, x, b, s);
+        if (!rc) rc = residual_berr(h, &berr, &den, s, &st);
         if (fused && first) {
             pert = (int64_t)st.perturbed;
             const int fst = ((st.flags & kFlagInternal) || st.abort) ? KKT_ERR_DEVICE
@@ -668,6 +658,7 @@ int fgmres_column(kkt_handle *h, const double *b, double *x, kkt_info *info, hip
         if (berr <= tol) { status = KKT_OK; break; }
         if (it >= h->opts.max_iters || !std::isfinite(berr)) { status = KKT_WARN_NOT_CONVERGED; break; }
         const double target = tol * den;
+        if (H.empty()) H.assign((size_t)(m + 1) * m, 0.0);
         double *beta2 = d.hbuf + 3 * (m + 2);
         enqueue_dots(h, 1, d.res, d.res, beta2, 0, s);
         timed(h, KKT_PROF_KRYLOV, s, [&] { k_scale_by_norm<<<nb, 256, 0, s>>>(n, d.res, beta2, d.V); });
@@ -787,7 +778,6 @@ int kkt_analyze(int32_t n, const int64_t *rowptr, const int32_t *colind, const d
     o.fixed_p = nullptr;   // borrowed for the call only
     o.fixed_q = nullptr;
     h->opts = o;
-    h->tickets = o.persistent_solve == 2;
     *out = h;
     return KKT_OK;
 }
@@ -801,7 +791,6 @@ int kkt_clone(const kkt_handle *src, kkt_handle **out) {
         h->opts = src->opts;
         h->sym = src->sym;
         h->sch = src->sch;
-        h->tickets = src->opts.persistent_solve == 2;
     } catch (const std::bad_alloc &) {
         delete h;
         return KKT_ERR_NOMEM;
@@ -920,9 +909,9 @@ int bind_common(kkt_handle *h, char *ws, size_t bytes, int32_t max_nrhs, hipStre
             hipFuncSetAttribute(reinterpret_cast<const void *>(&k_refactor_wide<MedCfg<T>>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, MedCfg<T>::kLds) != hipSuccess ||
             hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &bl, reinterpret_cast<const void *>(&k_lsolve_persistent<T, false>), kBlock, 0) != hipSuccess ||
+                &bl, reinterpret_cast<const void *>(&k_lsolve_persistent<T>), kPersThreads, 0) != hipSuccess ||
             hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &bu, reinterpret_cast<const void *>(&k_usolve_persistent<T, false>), kBlock, 0) != hipSuccess)
+                &bu, reinterpret_cast<const void *>(&k_usolve_persistent<T>), kPersThreads, 0) != hipSuccess)
             return -1;
         h->grid_l = std::max(1, bl) * std::max(1, ncu);
         h->grid_u = std::max(1, bu) * std::max(1, ncu);
@@ -930,11 +919,6 @@ int bind_common(kkt_handle *h, char *ws, size_t bytes, int32_t max_nrhs, hipStre
     });
     if (ok != 0) return KKT_ERR_DEVICE;
     h->ncu = std::max(1, ncu);
-    {
-        int coop = 0;
-        HIPCHK(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev));
-        if (!coop) h->tickets = true;   // the fixed item order needs a cooperative launch
-    }
     if (h->device >= 0 && h->device != dev) return KKT_ERR_STATE;   // rebinding keeps the device
     h->device = dev;
     h->bound = false;      // until the new workspace holds the structure
@@ -1058,13 +1042,13 @@ void record_levels(kkt_handle *h) {
     if (graph) (void)hipGraphDestroy(graph);
 }
 
-// records the level launches with the forward solve riding in them into h->fused; on any
-// failure kkt_refactor_refine runs the two calls
+// records the launches of a step (enqueue_step) into h->fused; on any failure they are
+// launched one by one
 void record_fused(kkt_handle *h) {
     hipGraph_t graph = nullptr;
     bool ok = hipStreamBeginCapture(h->cap, hipStreamCaptureModeThreadLocal) == hipSuccess;
     if (ok) {
-        const int rc = enqueue_levels(h, h->cap, true);
+        const int rc = enqueue_step(h, h->cap);
         const hipError_t e = hipStreamEndCapture(h->cap, &graph);
         ok = rc == KKT_OK && e == hipSuccess && graph &&
              hipGraphInstantiate(&h->fused, graph, nullptr, nullptr, 0) == hipSuccess;
@@ -1077,10 +1061,9 @@ void record_fused(kkt_handle *h) {
     if (graph) (void)hipGraphDestroy(graph);
 }
 
-// the level launches with the forward solve riding in them, replayed from h->fused (recorded
-// at the first call) or, without graphs, with the profiler on or on a capturing stream,
-// launched one by one
-int run_fused_levels(kkt_handle *h, hipStream_t s) {
+// the launches of a step, replayed from h->fused (recorded at the first call) or, without
+// graphs, with the profiler on or on a capturing stream, launched one by one
+int run_step(kkt_handle *h, hipStream_t s) {
     if (h->opts.graph_refactor && !h->prof && !h->fused_failed && !h->on_scratch) {
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         HIPCHK(hipStreamIsCapturing(s, &cs));
@@ -1093,7 +1076,7 @@ int run_fused_levels(kkt_handle *h, hipStream_t s) {
             }
         }
     }
-    return enqueue_levels(h, s, true);
+    return enqueue_step(h, s);
 }
 
 int run_levels(kkt_handle *h, hipStream_t s) {
@@ -1119,7 +1102,7 @@ int kkt_refactor(kkt_handle *h, const double *d_values, hipStream_t stream) {
     if (!h->bound) return KKT_ERR_STATE;
     DeviceGuard dg(h->device);
     if (!dg.ok) return KKT_ERR_DEVICE;
-    int rc = set_call(h, d_values, nullptr, stream);
+    int rc = set_call(h, d_values, nullptr, nullptr, stream);
     if (!rc) rc = run_levels(h, stream);
     if (rc) return rc;
     h->d_values = d_values;
@@ -1140,9 +1123,9 @@ int kkt_refactor_refine(kkt_handle *h, const double *d_values, const double *d_b
         HIPCHK(hipMemcpyAsync(d.bsave, b, sizeof(double) * n, hipMemcpyDeviceToDevice, stream));
         b = d.bsave;
     }
-    int rc = set_call(h, d_values, b, stream);
+    int rc = set_call(h, d_values, b, d_x, stream);
     if (rc) return rc;
-    rc = run_fused_levels(h, stream);
+    rc = run_step(h, stream);
     if (rc) return rc;
     h->d_values = d_values;
     h->factored = true;

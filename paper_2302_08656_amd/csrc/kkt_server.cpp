@@ -237,11 +237,9 @@ int kkt_server_create(const kkt_server_opts *opts, kkt_server **out) {
 int kkt_server_add_pattern(kkt_server *s, int32_t n, const int64_t *rowptr, const int32_t *colind,
                            const double *values_k1, const kkt_opts *opts, int32_t *pattern) {
     if (!s || !pattern) return KKT_ERR_ARG;
-    // several requests run at once: persistent solves take their items by ticket
     kkt_opts o;
     kkt_default_opts(&o);
     if (opts) o = *opts;
-    if (o.persistent_solve == 1) o.persistent_solve = 2;
     kkt_handle *h = nullptr;
     int rc = kkt_analyze(n, rowptr, colind, values_k1, &o, &h);
     if (rc) return rc;
