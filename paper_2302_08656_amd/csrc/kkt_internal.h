@@ -54,6 +54,11 @@ constexpr int kTinyR = 16;
 constexpr int kGroup = 32;
 constexpr int kMedW = 16;
 constexpr int kMedRows = 256;
+// Targets of one source pulled together by a medium item (one column tile of the matrix cores)
+constexpr int kWaveGroup = 16;
+// Most rows below a source, and of a factored panel, of a medium item that runs on one
+// wavefront; levels with longer ones keep 256-thread blocks, whose wavefronts share the rows
+constexpr int kWaveRows = 96;
 // rows of a factored panel up to which a 32-column wide item runs in a 256-thread block, and
 // the wide items a level needs for its launch to use 256-thread blocks (two per compute
 // unit): levels with fewer are bound by one item's latency, which 512 threads shorten
@@ -100,6 +105,9 @@ struct Schedule {
     // levels whose 32-column wide items run in 256-thread blocks (every factored panel of the
     // level has at most 256 rows): 1, else 0
     std::vector<int32_t> f_w256;
+    // levels whose medium items run on one wavefront each (no source and no factored panel has
+    // more than kWaveRows rows): 1, else 0
+    std::vector<int32_t> f_wave;
     // row-ordered copy: copy_k lists CSR positions, the strictly lower entries first (launch
     // l's: copy_k[copy_lat[l] .. copy_lat[l+1])), then the others (launch l's: copy_k[
     // copy_uat[l] .. copy_uat[l+1])), grouped by the launch that finishes their column;
@@ -117,13 +125,15 @@ struct Schedule {
     std::vector<int32_t> f_pair_pos;    // slot of the source's first row in the target column
     std::vector<int64_t> f_pair_rel;    // [npairs+1] range into f_rel
     std::vector<int32_t> f_rel;         // slot of each row R of the source in the target column
-    // packed records read by the refactorization kernels (8 x int32 each):
-    // itemrec[i] = {panel to factor or -1, first pair, end pair, panels factored, s, w, r,
-    //               ldiag[s], s', w', r', ldiag[s']} (s, w, r of the first panel; s', w', r' of
-    //               the first pair's source, zero for an item without pairs);
+    // packed records read by the refactorization kernels:
+    // itemrec[i] (16 x int32) = {panel to factor or -1, first pair, end pair, panels factored,
+    //               s, w, r, ldiag[s], then for wide items s', w', r', ldiag[s'], 0, 0, 0, 0
+    //               (s, w, r of the first panel; s', w', r' of the first pair's source), for
+    //               narrow items the first pair's record; zeros for an item without pairs};
     // pair8[q] = {source panel, f_pair_pos, f_pair_rel (first index), end of q's group,
     //             s, w, r, ldiag[s]}, with s, w, r the panel's first column, width, rows below
-    //             (a group: consecutive pairs of one source, at most kGroup);
+    //             (a group: consecutive pairs of one source, at most kGroup, on levels with
+    //             f_wave at most kWaveGroup);
     // for pairs of narrow items {ldiag[s+1], f_pair_pos, f_pair_rel, ldiag[s+2], ldiag[s+3],
     //             w, r, ldiag[s]} (slots past the width are 0)
     std::vector<int32_t> itemrec, pair8;

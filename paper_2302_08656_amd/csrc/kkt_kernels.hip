@@ -51,9 +51,113 @@ __device__ __forceinline__ void atomic_max_pos(double *addr, double v) {
     atomicMax(reinterpret_cast<unsigned long long *>(addr), (unsigned long long)__double_as_longlong(v));
 }
 
+// Cross-lane moves on the vector ALU (DPP and the permlane swaps): a few cycles each, where a
+// shuffle is a round trip through the LDS unit (over 100 cycles) on chains that are nothing but
+// latency.  ctrl: the DPP control; bank: which quads of each 16-lane row are written, the others
+// keep old.
+template <int ctrl, int bank = 0xf>
+__device__ __forceinline__ int dpp(int old, int v) {
+    return __builtin_amdgcn_update_dpp(old, v, ctrl, 0xf, bank, false);
+}
+constexpr int kDppRowRor = 0x120;        // + n: lane i of a row takes lane (i - n) mod 16
+constexpr int kDppRowNewBcast = 0x150;   // + n: every lane of a row takes lane n
+
+// the value of lane i ^ kO (kO = 1, 2, 4, 8)
+template <int kO>
+__device__ __forceinline__ int lane_xor(int v) {
+    if constexpr (kO == 1) return dpp<0xb1>(v, v);                 // quad_perm 1 0 3 2
+    else if constexpr (kO == 2) return dpp<0x4e>(v, v);            // quad_perm 2 3 0 1
+    else if constexpr (kO == 4) return dpp<kDppRowRor + 4, 0xa>(dpp<kDppRowRor + 12, 0x5>(v, v), v);
+    else return dpp<kDppRowRor + 8>(v, v);
+}
+template <int kO>
+__device__ __forceinline__ double lane_xor(double v) {
+    return __hiloint2double(lane_xor<kO>(__double2hiint(v)), lane_xor<kO>(__double2loint(v)));
+}
+// v of this lane plus v of lane i ^ kO (kO = 16, 32)
+template <int kO>
+__device__ __forceinline__ double add_far(double v) {
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+    u2 l, h;   // {the even half's or row's value, the odd one's} in both
+    if constexpr (kO == 16) {
+        l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+        h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    } else {
+        l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+        h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    }
+    return __hiloint2double((int)h.x, (int)l.x) + __hiloint2double((int)h.y, (int)l.y);
+}
+
+// p[i] where ok, else 0: the address is selected instead of the load being skipped, because a
+// divergent branch around every load costs more than the loads (the kernels here run a few
+// wavefronts per SIMD through short code, bound by its latency)
+// kMask: the load is skipped on the lanes where not ok, for launches with more items than the
+// device holds at once, which the memory pipeline bounds.
+template <bool kMask = false, class T>
+__device__ __forceinline__ T load_if(const T *p, int i, bool ok) {
+    if constexpr (kMask) {
+        T v = T(0);
+        if (ok) v = p[i];
+        return v;
+    } else {
+        const T v = p[ok ? i : 0];
+        return ok ? v : T(0);
+    }
+}
+
+// the sum over aligned groups of `width` lanes (a power of two, the same for the wavefront),
+// farthest lanes first, on every lane
 __device__ __forceinline__ double group_sum(double v, int width) {
-    for (int o = width / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, width);
+    if (width > 32) v = add_far<32>(v);
+    if (width > 16) v = add_far<16>(v);
+    if (width > 8) v += lane_xor<8>(v);
+    if (width > 4) v += lane_xor<4>(v);
+    if (width > 2) v += lane_xor<2>(v);
+    if (width > 1) v += lane_xor<1>(v);
     return v;
+}
+
+// the value of lane j (a constant once unrolled) of each aligned group of kL = 4 or 16 lanes
+template <int kL>
+__device__ __forceinline__ int group_bcast(int v, int j) {
+    static_assert(kL == 4 || kL == 16, "a quad or a row");
+    if constexpr (kL == 4) {
+        switch (j) {
+            case 0: return dpp<0x00>(v, v);
+            case 1: return dpp<0x55>(v, v);
+            case 2: return dpp<0xaa>(v, v);
+            default: return dpp<0xff>(v, v);
+        }
+    } else {
+        switch (j) {
+            case 0: return dpp<kDppRowNewBcast + 0>(v, v);
+            case 1: return dpp<kDppRowNewBcast + 1>(v, v);
+            case 2: return dpp<kDppRowNewBcast + 2>(v, v);
+            case 3: return dpp<kDppRowNewBcast + 3>(v, v);
+            case 4: return dpp<kDppRowNewBcast + 4>(v, v);
+            case 5: return dpp<kDppRowNewBcast + 5>(v, v);
+            case 6: return dpp<kDppRowNewBcast + 6>(v, v);
+            case 7: return dpp<kDppRowNewBcast + 7>(v, v);
+            case 8: return dpp<kDppRowNewBcast + 8>(v, v);
+            case 9: return dpp<kDppRowNewBcast + 9>(v, v);
+            case 10: return dpp<kDppRowNewBcast + 10>(v, v);
+            case 11: return dpp<kDppRowNewBcast + 11>(v, v);
+            case 12: return dpp<kDppRowNewBcast + 12>(v, v);
+            case 13: return dpp<kDppRowNewBcast + 13>(v, v);
+            case 14: return dpp<kDppRowNewBcast + 14>(v, v);
+            default: return dpp<kDppRowNewBcast + 15>(v, v);
+        }
+    }
+}
+template <int kL>
+__device__ __forceinline__ double group_bcast(double v, int j) {
+    return __hiloint2double(group_bcast<kL>(__double2hiint(v), j), group_bcast<kL>(__double2loint(v), j));
+}
+template <int kL>
+__device__ __forceinline__ float group_bcast(float v, int j) {
+    return __int_as_float(group_bcast<kL>(__float_as_int(v), j));
 }
 
 // ---------------------------------------------------------------------------------------
@@ -442,10 +546,12 @@ template <class T> struct Pair;
 template <> struct Pair<double> { using type = double2; };
 template <> struct Pair<float> { using type = float2; };
 
-// Packed records, an item three int4, a pair two:
-//   item[3i]   = {panel to factor or -1, first pair, end of pairs, panels factored}
-//   item[3i+1] = {its first column s, width w, rows below r, slot of the diagonal of column s}
-//   item[3i+2] = the same for the source of its first pair (zero without pairs)
+// Packed records, an item four int4, a pair two:
+//   item[4i]   = {panel to factor or -1, first pair, end of pairs, panels factored}
+//   item[4i+1] = {its first column s, width w, rows below r, slot of the diagonal of column s}
+//   item[4i+2] = wide items: the same for the source of the first pair (zero without pairs);
+//                narrow items: the first pair's record (with item[4i+3]), so that an item with
+//                one pair, as most have, waits for one round of metadata instead of two
 // An item that factors several panels (consecutive panels of one supernode) factors them in
 // order; its pairs list the pulls from outside first, then the pulls of each of its panels
 // into the later ones, by source: a panel is factored before the first pull whose source
@@ -494,6 +600,15 @@ __device__ __forceinline__ T perturb(T p, T thresh, int &npert) {
 
 // ----------------------------------------------------------------- 16-lane path
 
+// Orders this wavefront's memory operations before its later ones for its other lanes: they
+// leave in program order and operations of a wavefront on one address stay in order, so this
+// is a compiler fence that emits no wait.
+__device__ __forceinline__ void wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Source side of the update of target column k by a narrow source panel S (w <= kSmallW,
 // r <= kSmallRows * kL), loaded by one group of kL lanes (16, or 4 for tiny items): S's
 // diagonal block rows, its L rows and the slots of those rows in the target; lane gl holds
@@ -510,128 +625,156 @@ struct SmallSrc {
 };
 
 // pa, pb: the pair's record {ldiag[s+1], pos, rel, ldiag[s+2]}, {ldiag[s+3], w, r, ldiag[s]}
-template <int kL, class T>
+template <int kL, bool kMask, class T>
 __device__ __forceinline__ void small_load_src(const RefArgs<T> &a, int4 pa, int4 pb, int gl, SmallSrc<T> &x) {
     const int ld[kSmallW] = {pb.w, pa.x, pa.w, pb.x};
     x.ps = pa.y;
     x.w = pb.y;
     x.r = pb.z;
     const int w = x.w, r = x.r;
-    const int32_t *rel = a.rel + pa.z;
+    const int32_t *rel = a.rel + (r > 0 ? pa.z : 0);
 #pragma unroll
-    for (int j = 0; j < kSmallW - 1; ++j) x.l_row[j] = (j + 1 < w && gl > j && gl < w) ? a.lu[ld[j] + (gl - j)] : T(0);
+    for (int j = 0; j < kSmallW - 1; ++j) x.l_row[j] = load_if<kMask>(a.lu, ld[j] + (gl - j), j + 1 < w && gl > j && gl < w);
 #pragma unroll
     for (int k = 0; k < kSmallRows; ++k) {
         const int i = gl + kL * k;
-        x.pos[k] = i < r ? rel[i] : 0;
+        x.pos[k] = 0;
 #pragma unroll
-        for (int j = 0; j < kSmallW; ++j) x.lr[k][j] = (i < r && j < w) ? a.lu[ld[j] + 1 + (w - 1 - j) + i] : T(0);
+        for (int j = 0; j < kSmallW; ++j) x.lr[k][j] = T(0);
+        if (k == 0 || __any(i < r)) {   // the same for the wavefront
+            x.pos[k] = load_if<kMask>(rel, i, i < r);
+#pragma unroll
+            for (int j = 0; j < kSmallW; ++j) x.lr[k][j] = load_if<kMask>(a.lu, ld[j] + (w - j) + i, i < r && j < w);
+        }
     }
 }
 
-// Target side: rows s..s+w-1 of column k (from slot ps on) become final U entries (unit
-// lower solve with S's diagonal block) and the rows R of S lose L(R, S) times them.
-template <int kL, class T>
-__device__ __forceinline__ void small_apply(const RefArgs<T> &a, const SmallSrc<T> &x, int gl) {
-    const int w = x.w, r = x.r;
-    // one round: the target's rows of S and of R
-    T u = gl < w ? a.lu[x.ps + gl] : T(0);
+// The target column's values at the rows of S (from slot ps on) and at the rows R of S.
+template <class T>
+struct SmallTgt {
+    T u;
     T tv[kSmallRows];
-#pragma unroll
-    for (int k = 0; k < kSmallRows; ++k) tv[k] = gl + kL * k < r ? a.lu[x.pos[k]] : T(0);
-#pragma unroll
-    for (int j = 0; j < kSmallW - 1; ++j) {
-        const T uj = __shfl(u, j, kL);
-        if (j + 1 < w && gl > j && gl < w) u = fma(-x.l_row[j], uj, u);
-    }
-    if (gl < w) a.lu[x.ps + gl] = u;
-    T uu[kSmallW];
-#pragma unroll
-    for (int j = 0; j < kSmallW; ++j) uu[j] = __shfl(u, j, kL);
+};
+template <int kL, bool kMask, class T>
+__device__ __forceinline__ void small_load_tgt(const RefArgs<T> &a, const SmallSrc<T> &x, int gl, SmallTgt<T> &y) {
+    y.u = load_if<kMask>(a.lu, x.ps + gl, gl < x.w);
 #pragma unroll
     for (int k = 0; k < kSmallRows; ++k) {
-        if (gl + kL * k < r) {
+        const bool ok = gl + kL * k < x.r;
+        y.tv[k] = T(0);
+        if (k == 0 || __any(ok)) y.tv[k] = load_if<kMask>(a.lu, x.pos[k], ok);
+    }
+}
+
+// Target side: rows s..s+w-1 of column k become final U entries (unit lower solve with S's
+// diagonal block) and the rows R of S lose L(R, S) times them.
+template <int kL, class T>
+__device__ __forceinline__ void small_apply(const RefArgs<T> &a, const SmallSrc<T> &x, const SmallTgt<T> &y, int gl) {
+    const int w = x.w, r = x.r;
+    T u = y.u;
+#pragma unroll
+    for (int j = 0; j < kSmallW - 1; ++j) {
+        const T nu = fma(-x.l_row[j], group_bcast<kL>(u, j), u);
+        u = j + 1 < w && gl > j && gl < w ? nu : u;
+    }
+    if (gl < w) a.lu[x.ps + gl] = u;
+    T uu[kSmallW];   // zero past w, as are the entries of lr
+#pragma unroll
+    for (int j = 0; j < kSmallW; ++j) uu[j] = group_bcast<kL>(u, j);
+#pragma unroll
+    for (int k = 0; k < kSmallRows; ++k) {
+        const bool ok = gl + kL * k < r;
+        if (k == 0 || __any(ok)) {
             T acc = T(0);
 #pragma unroll
-            for (int j = 0; j < kSmallW; ++j)
-                if (j < w) acc = fma(x.lr[k][j], uu[j], acc);
-            a.lu[x.pos[k]] = tv[k] - acc;
+            for (int j = 0; j < kSmallW; ++j) acc = fma(x.lr[k][j], uu[j], acc);
+            if (ok) a.lu[x.pos[k]] = y.tv[k] - acc;
         }
     }
-    __threadfence_block();   // a later source of the same column may read these rows
+    // a later source of the same column, and the panel's factorization, read these rows: they
+    // are read by this wavefront, whose memory operations on one address keep their order, so
+    // nothing waits for the stores to arrive
+    wave_order();
 }
 
 // Dense LU without pivoting of a narrow panel's block column (w <= kSmallW,
 // r <= kSmallRows * kL) by a group of kL lanes.  pn = {s, w, r, slot of the first
 // diagonal}.  Returns the number of replaced pivots (the same value on every lane of the
 // group).
-template <int kL, class T>
+template <int kL, bool kMask, class T>
 __device__ __forceinline__ int small_factor(const RefArgs<T> &a, int4 pn, int ldg, int gl, T thresh) {
     const int w = pn.y, r = pn.z;
     int sg[kSmallW];
 #pragma unroll
-    for (int c = 0; c < kSmallW; ++c) sg[c] = __shfl(ldg, c, kL) - c;
+    for (int c = 0; c < kSmallW; ++c) sg[c] = group_bcast<kL>(ldg, c) - c;
     // one round: the diagonal block (lane gl < w holds row gl) and this lane's rows below
     T d[kSmallW];
 #pragma unroll
-    for (int c = 0; c < kSmallW; ++c) d[c] = (c < w && gl < w) ? a.lu[sg[c] + gl] : T(0);
+    for (int c = 0; c < kSmallW; ++c) d[c] = load_if<kMask>(a.lu, sg[c] + gl, c < w && gl < w);
     constexpr int kRows = kSmallRows;
     T x[kRows][kSmallW];
 #pragma unroll
-    for (int k = 0; k < kRows; ++k)
+    for (int k = 0; k < kRows; ++k) {
+        const bool ok = gl + kL * k < r;
 #pragma unroll
-        for (int c = 0; c < kSmallW; ++c) x[k][c] = (c < w && gl + kL * k < r) ? a.lu[sg[c] + w + gl + kL * k] : T(0);
+        for (int c = 0; c < kSmallW; ++c) x[k][c] = T(0);
+        if (k == 0 || __any(ok)) {
+#pragma unroll
+            for (int c = 0; c < kSmallW; ++c) x[k][c] = load_if<kMask>(a.lu, sg[c] + w + gl + kL * k, c < w && ok);
+        }
+    }
     int npert = 0, bad = 0;
-    T U[kSmallW][kSmallW];   // final U of the diagonal block, known to every lane
+    // step jj (run while any panel of the wavefront has a column jj): U[c] is the pivot row,
+    // known to every lane of the group
 #pragma unroll
     for (int jj = 0; jj < kSmallW; ++jj) {
-        if (jj < w) {
-            T ur[kSmallW];
+        if (jj == 0 || __any(jj < w)) {
+            T U[kSmallW];
 #pragma unroll
-            for (int c = 0; c < kSmallW; ++c) ur[c] = __shfl(d[c], jj, kL);
-            const T p = perturb(ur[jj], thresh, npert);
-            bad |= !isfinite(p);
-            if (gl == jj) d[jj] = p;
-            ur[jj] = p;
+            for (int c = jj; c < kSmallW; ++c) U[c] = group_bcast<kL>(d[c], jj);
+            int np = 0;
+            U[jj] = perturb(U[jj], thresh, np);
+            npert += jj < w ? np : 0;
+            bad |= jj < w && !isfinite(U[jj]);
+            const bool lo = gl > jj && gl < w;
+            const T l = d[jj] / U[jj];
+            d[jj] = lo ? l : gl == jj && jj < w ? U[jj] : d[jj];
 #pragma unroll
-            for (int c = 0; c < kSmallW; ++c) U[jj][c] = ur[c];
-            if (gl > jj && gl < w) {
-                const T l = d[jj] / p;
-                d[jj] = l;
-#pragma unroll
-                for (int c = jj + 1; c < kSmallW; ++c)
-                    if (c < w) d[c] = fma(-l, ur[c], d[c]);
+            for (int c = jj + 1; c < kSmallW; ++c) {
+                const T nd = fma(-l, U[c], d[c]);
+                d[c] = lo ? nd : d[c];
             }
-        }
-    }
-    if (gl < w) {
 #pragma unroll
-        for (int c = 0; c < kSmallW; ++c)
-            if (c < w) a.lu[sg[c] + gl] = d[c];
-    }
+            for (int k = 0; k < kRows; ++k) {
+                const bool ok = gl + kL * k < r && jj < w;
+                if (k == 0 || __any(ok)) {
+                    const T lx = x[k][jj] / U[jj];
+                    bad |= ok && !isfinite(lx);
+                    x[k][jj] = ok ? lx : x[k][jj];
 #pragma unroll
-    for (int k = 0; k < kRows; ++k) {
-        if (gl + kL * k < r) {
-#pragma unroll
-            for (int jj = 0; jj < kSmallW; ++jj) {
-                if (jj < w) {
-                    const T l = x[k][jj] / U[jj][jj];
-                    bad |= !isfinite(l);
-                    x[k][jj] = l;
-#pragma unroll
-                    for (int c = jj + 1; c < kSmallW; ++c)
-                        if (c < w) x[k][c] = fma(-l, U[jj][c], x[k][c]);
+                    for (int c = jj + 1; c < kSmallW; ++c) {
+                        const T nx = fma(-lx, U[c], x[k][c]);
+                        x[k][c] = ok ? nx : x[k][c];
+                    }
                 }
             }
-#pragma unroll
-            for (int c = 0; c < kSmallW; ++c)
-                if (c < w) a.lu[sg[c] + w + gl + kL * k] = x[k][c];
         }
     }
+#pragma unroll
+    for (int c = 0; c < kSmallW; ++c)
+        if (c < w) {
+            if (gl < w) a.lu[sg[c] + gl] = d[c];
+#pragma unroll
+            for (int k = 0; k < kRows; ++k)
+                if (gl + kL * k < r) a.lu[sg[c] + w + gl + kL * k] = x[k][c];
+        }
     if (bad) atomicOr(&a.st->flags, kFlagNonfinite);
     return npert;
 }
 
+// Bound by the latency of its rounds; measured per level of the 200-bus grid (100 to 900 items
+// of one to four pairs): 10-12 us with a branch around every load and sum, LDS shuffles and a
+// wait for each pair's stores, 6.6 us in this form.
 // One item per group of kL lanes (16; 4 for tiny items, whose panels have at most kTinyR
 // rows below, so a wavefront keeps four times as many of them in flight).  kPipe: the next
 // pair's source side is loaded while the current pair is applied (fewer dependent rounds
@@ -640,62 +783,81 @@ __device__ __forceinline__ int small_factor(const RefArgs<T> &a, int4 pn, int ld
 // perturbed pivots go to counter slot `slot`.  No block-wide synchronisation: the groups of
 // a block are independent.  Every entry receives the same operations in the same order
 // whatever kL is.
-template <class T, bool kPipe, int kL = 16>
+template <class T, bool kPipe, bool kMask, int kL = 16>
 __device__ __forceinline__ void small_group(int item0, int nsmall, const RefArgs<T> &a, int g, int slot) {
     const T thresh = pivot_threshold(a);
     const int gl = threadIdx.x & (kL - 1);
     int npert = 0;
     if (g < nsmall) {
         const int item = item0 + g;
-        const int4 ia = a.item[3 * item], ib = a.item[3 * item + 1];
-        // one round: the records of up to kL pairs (lane t holds pair p0 + t) and the
-        // diagonal slots of the panel to factor
+        const int4 ia = a.item[4 * item], ib = a.item[4 * item + 1];
+        const int4 fa = a.item[4 * item + 2], fb = a.item[4 * item + 3];   // the first pair
+        // one round: the records of up to kL further pairs (lane t holds pair p0 + 1 + t) and
+        // the diagonal slots of the panel to factor, beside the first pair's operands
         const int p0 = ia.y, np = ia.z - ia.y;
         int4 ra = int4{0, 0, 0, 0}, rb = int4{0, 0, 0, 0};
-        if (gl < np) {
-            ra = a.pair[2 * (p0 + gl)];
-            rb = a.pair[2 * (p0 + gl) + 1];
+        if (gl + 1 < np) {
+            ra = a.pair[2 * (p0 + 1 + gl)];
+            rb = a.pair[2 * (p0 + 1 + gl) + 1];
         }
         const int ldg = (ia.x >= 0 && ib.y > 1 && gl > 0 && gl < ib.y) ? a.ldiag[ib.x + gl] : ib.w;
-        auto rec = [&](int q, int4 &pa, int4 &pb) {
-            if (q >= kL) {   // items with more than kL pairs read the rest on demand
+        auto rec = [&](int q, int4 &pa, int4 &pb) {   // pair q >= 1
+            if (q > kL) {   // items with more than kL + 1 pairs read the rest on demand
                 pa = a.pair[2 * (p0 + q)];
                 pb = a.pair[2 * (p0 + q) + 1];
                 return;
             }
-            pa = int4{__shfl(ra.x, q, kL), __shfl(ra.y, q, kL), __shfl(ra.z, q, kL), __shfl(ra.w, q, kL)};
-            pb = int4{__shfl(rb.x, q, kL), __shfl(rb.y, q, kL), __shfl(rb.z, q, kL), __shfl(rb.w, q, kL)};
+            const int t = q - 1;
+            pa = int4{__shfl(ra.x, t, kL), __shfl(ra.y, t, kL), __shfl(ra.z, t, kL), __shfl(ra.w, t, kL)};
+            pb = int4{__shfl(rb.x, t, kL), __shfl(rb.y, t, kL), __shfl(rb.z, t, kL), __shfl(rb.w, t, kL)};
         };
         if constexpr (kPipe) {
             if (np > 0) {
                 SmallSrc<T> cur, nxt;
-                int4 pa, pb;
-                rec(0, pa, pb);
-                small_load_src<kL>(a, pa, pb, gl, cur);
+                SmallTgt<T> tgt;
+                small_load_src<kL, kMask>(a, fa, fb, gl, cur);
+                // each lane touches the source, slots and target of its pair, so that the pairs
+                // after the next one find theirs in the L2 cache instead of each waiting for
+                // memory (loads return in order: these come after the first operands)
+                T tl = T(0), tt = T(0);
+                int tr = 0;
                 for (int q = 0; q < np; ++q) {
+                    small_load_tgt<kL, kMask>(a, cur, gl, tgt);
                     if (q + 1 < np) {
+                        int4 pa, pb;
                         rec(q + 1, pa, pb);
-                        small_load_src<kL>(a, pa, pb, gl, nxt);
+                        small_load_src<kL, kMask>(a, pa, pb, gl, nxt);
                     }
-                    small_apply<kL>(a, cur, gl);
+                    if (q == 0 && gl + 2 < np) {
+                        tl = a.lu[rb.w];
+                        tr = a.rel[rb.z > 0 ? ra.z : 0];
+                        tt = a.lu[ra.y];
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    small_apply<kL>(a, cur, tgt, gl);
                     cur = nxt;
                 }
+                asm volatile("" ::"v"(tl), "v"(tt), "v"(tr));   // the touches stay
             }
         } else {
             for (int q = 0; q < np; ++q) {
                 SmallSrc<T> cur;
-                int4 pa, pb;
-                rec(q, pa, pb);
-                small_load_src<kL>(a, pa, pb, gl, cur);
-                small_apply<kL>(a, cur, gl);
+                SmallTgt<T> tgt;
+                int4 pa = fa, pb = fb;
+                if (q > 0) rec(q, pa, pb);
+                small_load_src<kL, kMask>(a, pa, pb, gl, cur);
+                small_load_tgt<kL, kMask>(a, cur, gl, tgt);
+                small_apply<kL>(a, cur, tgt, gl);
             }
         }
-        if (ia.x >= 0) npert = small_factor<kL>(a, ib, ldg, gl, thresh);
+        if (ia.x >= 0) npert = small_factor<kL, kMask>(a, ib, ldg, gl, thresh);
     }
-    // one counter update per wavefront: group leaders contribute their count
+    // one counter update per wavefront (rarely any): group leaders contribute their count
     int c = gl == 0 ? npert : 0;
-    for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
-    if ((threadIdx.x & 63) == 0 && c) atomicAdd(&a.pcount[slot % kCountSlots], (unsigned long long)c);
+    if (__any(c)) {
+        for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
+        if ((threadIdx.x & 63) == 0) atomicAdd(&a.pcount[slot % kCountSlots], (unsigned long long)c);
+    }
 }
 
 template <class T>
@@ -707,7 +869,7 @@ __device__ __forceinline__ void copy_block(const RefArgs<T> &a, const CopyRanges
 // first blocks run the others, kBlock / 16 to a block, the next ones the tiny items,
 // kBlock / kTinyLanes to a block; the blocks after them copy the ranges c of the
 // row-ordered factor (columns final before the launch)
-template <class T, bool kPipe>
+template <class T, bool kPipe, bool kMask>
 __global__ __launch_bounds__(256) void k_refactor_small(int item0, int nsmall, int ntiny, RefArgs<T> a,
                                                         CopyRanges c) {
     const int nn = nsmall - ntiny;
@@ -715,9 +877,9 @@ __global__ __launch_bounds__(256) void k_refactor_small(int item0, int nsmall, i
     const int ntb = (ntiny + kBlock / kTinyLanes - 1) / (kBlock / kTinyLanes);
     const int b = blockIdx.x, slot = b * 4 + (threadIdx.x >> 6);
     if (b < nsb) {
-        small_group<T, kPipe>(item0, nn, a, b * (kBlock / 16) + (threadIdx.x >> 4), slot);
+        small_group<T, kPipe, kMask>(item0, nn, a, b * (kBlock / 16) + (threadIdx.x >> 4), slot);
     } else if (b < nsb + ntb) {
-        small_group<T, kPipe, kTinyLanes>(item0 + nn, ntiny, a,
+        small_group<T, kPipe, kMask, kTinyLanes>(item0 + nn, ntiny, a,
                                           (b - nsb) * (kBlock / kTinyLanes) + (threadIdx.x / kTinyLanes), slot);
     } else {
         copy_block(a, c, b - nsb - ntb, gridDim.x - nsb - ntb, kBlock);
@@ -1052,7 +1214,7 @@ __device__ __forceinline__ void wide_item(const int item, const RefArgs<typename
     int *ldsb = reinterpret_cast<int *>(sm + C::kOffLds);
     int *sgs = reinterpret_cast<int *>(sm + C::kOffSgs);
     int4 *prs = reinterpret_cast<int4 *>(sm + C::kOffPairs);
-    const int4 ia = a.item[3 * item], ib = a.item[3 * item + 1], ic = a.item[3 * item + 2];
+    const int4 ia = a.item[4 * item], ib = a.item[4 * item + 1], ic = a.item[4 * item + 2];
     const int pbeg = ia.y, p1 = ia.z;
     const int npan = ia.x >= 0 ? max(1, ia.w) : 0;
     int done = 0;   // panels of the item factored so far
@@ -1295,6 +1457,250 @@ __device__ __forceinline__ void wide_item(const int item, const RefArgs<typename
     while (done < npan) factor_next();
 }
 
+// ------------------------------------------------------------- wavefront path (medium items)
+
+// A medium item (every panel involved at most kMedW columns, the factored one at most kMedRows
+// rows) on one wavefront: no block barrier, the operands of the matrix-core updates loaded from
+// the factor straight into their lanes, and a quarter of the 256-thread form's registers and LDS
+// per item, so that four times as many are in flight.  A group is one source and up to kWaveT
+// targets.  An update's products and sums are those of the wide path, in its order.
+constexpr int kWaveT = kWaveGroup;
+constexpr int kUbLd = kWaveT + 2;   // LDS row stride of the solved rows of one target
+template <class T>
+struct WaveLds {
+    T Ub[kWaveT * kUbLd];    // solved rows per target
+    T Us[kMedW * kMedW];     // the panel's U rows, for its rows past the first 64
+};
+
+// Dense LU without pivoting of a panel of w <= KW columns and nrow rows, row = lane for the
+// first 64; sgl: lane c < w holds the slot of the panel's first row in column c.  A row's
+// window moves down one register per step, as in the wide sweep, and narrows to half of KW for
+// the last KW / 2 steps.  The pivot row is broadcast by readlane (scalar operands of the
+// updates), so a step waits for no memory: multipliers are stored as they come, the U rows go
+// to LDS and from there to the factor, in whole rows.  Returns the number of replaced pivots.
+template <int KW, class T>
+__device__ __forceinline__ int wave_factor(const RefArgs<T> &a, int w, int nrow, int sgl, T *Us, T thresh) {
+    using P2 = typename Pair<T>::type;
+    const int lane = threadIdx.x & 63;
+    T x[KW];
+#pragma unroll
+    for (int c = 0; c < KW; ++c) {
+        const int sc = __builtin_amdgcn_readlane(sgl, c);
+        x[c] = load_if(a.lu, sc + lane, c < w && lane < nrow);
+    }
+    int npert = 0;
+    T fin = T(0);   // not a number once a pivot or multiplier is not finite
+    auto run = [&](auto kc, int j0, int j1) {
+        constexpr int K = decltype(kc)::value;
+#pragma unroll 1
+        for (int j = j0; j < j1; ++j) {
+            T p = bcast(x[0], j);
+            T u[K];
+#pragma unroll
+            for (int c = 1; c < K; ++c) u[c] = bcast(x[c], j);
+            const int sj = __builtin_amdgcn_readlane(sgl, j);
+            p = perturb(p, thresh, npert);
+            if (lane == j) {
+                P2 *o = reinterpret_cast<P2 *>(Us + j * KW);
+                o[0] = P2{p, x[1]};
+#pragma unroll
+                for (int c = 1; c < K / 2; ++c) o[c] = P2{x[2 * c], x[2 * c + 1]};
+            }
+            const T l = x[0] / p;
+            // rows up to the pivot are done: what their registers hold is not read again
+#pragma unroll
+            for (int c = 1; c < K; ++c) x[c - 1] = fma(-l, u[c], x[c]);
+            x[K - 1] = T(0);
+            if (lane > j && lane < nrow) {
+                fin = fma(l, T(0), fin);
+                a.lu[sj + lane] = l;
+            }
+            fin = fma(p, T(0), fin);
+        }
+    };
+    const int jh = max(0, w - KW / 2);
+    run(std::integral_constant<int, KW>{}, 0, jh);
+    run(std::integral_constant<int, KW / 2>{}, jh, w);
+    wave_order();
+    // U(j, j + c) = Us[j KW + c]
+#pragma unroll 1
+    for (int t = lane; t < w * KW; t += 64) {
+        const int j = t / KW, c = t % KW;
+        const int sc = __shfl(sgl, min(j + c, w - 1));
+        if (c < (j < jh ? KW : KW / 2) && j + c < w) a.lu[sc + j] = Us[t];
+    }
+#pragma unroll 1
+    for (int row = lane + 64; row < nrow; row += 64) {
+#pragma unroll
+        for (int c = 0; c < KW; ++c) {
+            const int sc = __builtin_amdgcn_readlane(sgl, c);
+            x[c] = load_if(a.lu, sc + row, c < w);
+        }
+#pragma unroll 1
+        for (int j = 0; j < w; ++j) {
+            const T l = x[0] / Us[j * KW];
+            fin = fma(l, T(0), fin);
+            a.lu[__builtin_amdgcn_readlane(sgl, j) + row] = l;
+            const int kj = j < jh ? KW : KW / 2;
+#pragma unroll
+            for (int c = 1; c < KW; ++c) x[c - 1] = c < kj ? fma(-l, Us[j * KW + c], x[c]) : T(0);
+        }
+    }
+    if (__any(fin != T(0)) && lane == 0) atomicOr(&a.st->flags, kFlagNonfinite);
+    return npert;
+}
+
+// One medium item: its pulls, group by group, then its panel's factorization.  slot: counter
+// slot of the replaced pivots.  item is the same for the wavefront.
+template <class T>
+__device__ __forceinline__ void wave_item(int item, const RefArgs<T> &a, WaveLds<T> &L, int slot) {
+    using MM = Mfma<T>;
+    const T thresh = pivot_threshold(a);
+    const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+    constexpr int kKs = kMedW / 4;     // k steps of an update tile
+    constexpr int kRd = kWaveT / 4;    // rounds of four targets of the lower solve
+    constexpr int kTl = 2;             // row tiles per pass
+    const int4 ia = a.item[4 * item], ib = a.item[4 * item + 1], ic = a.item[4 * item + 2];
+    const int p1 = __builtin_amdgcn_readfirstlane(ia.z);
+    int sgl = 0;
+    if (ia.x >= 0 && li < ib.y) sgl = a.ldiag[ib.x + li] - li;
+    // a group's metadata: its first record's end of group, each lane's target slots (target
+    // 4k + lk) and first slot index (target li), the diagonal slots of columns 4k + lk of S
+    int g0 = __builtin_amdgcn_readfirstlane(ia.y);
+    int gend = 0, relb = 0, pos[kRd], ldj[kKs];
+    int4 geo = ic;
+    auto load_pairs = [&](int g) {
+        gend = a.pair[2 * g].w;
+        relb = a.pair[2 * min(g + li, p1 - 1)].z;
+#pragma unroll
+        for (int k = 0; k < kRd; ++k) pos[k] = a.pair[2 * min(g + 4 * k + lk, p1 - 1)].y;
+    };
+    auto load_diag = [&]() {
+#pragma unroll
+        for (int k = 0; k < kKs; ++k) ldj[k] = 4 * k + lk < geo.y ? a.ldiag[geo.x + 4 * k + lk] : 0;
+    };
+    if (g0 < p1) {
+        load_pairs(g0);
+        load_diag();
+    }
+    while (g0 < p1) {
+        const int g1 = __builtin_amdgcn_readfirstlane(gend), m = g1 - g0;
+        const int w = __builtin_amdgcn_readfirstlane(geo.y), r = __builtin_amdgcn_readfirstlane(geo.z);
+        // one round: L_SS (lane li holds row li: L(li, j), j < li), the rows of S in the targets,
+        // the first pass's L rows (row tile t, k step s: row 16 t + li, column 4 s + lk) and
+        // destination slots
+        T lc[kMedW - 1], u[kRd], av[kTl][kKs], cur[kTl][4];
+        int q[kTl][4];
+        auto load_rows = [&](int i0) {
+#pragma unroll
+            for (int t = 0; t < kTl; ++t) {
+                const int row = i0 + 16 * t + li;
+#pragma unroll
+                for (int s = 0; s < kKs; ++s) {
+                    const int j = 4 * s + lk;
+                    const bool ok = row < r && j < w;
+                    const T v = a.lu[ok ? ldj[s] + (w - j) + row : 0];
+                    av[t][s] = ok ? v : T(0);
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int i = i0 + 16 * t + MM::row(lk, v);
+                    const bool ok = li < m && i < r;
+                    const int x = a.rel[ok ? relb + i : 0];
+                    q[t][v] = ok ? x : -1;
+                }
+            }
+        };
+        auto load_cur = [&]() {
+#pragma unroll
+            for (int t = 0; t < kTl; ++t)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) cur[t][v] = a.lu[max(q[t][v], 0)];
+        };
+#pragma unroll
+        for (int j = 0; j + 1 < kMedW; ++j) {
+            const int dj = __builtin_amdgcn_readlane(ldj[j >> 2], (j & 3) * 16);
+            const bool ok = li > j && li < w;
+            const T v = a.lu[ok ? dj + (li - j) : 0];
+            lc[j] = ok ? v : T(0);
+        }
+#pragma unroll
+        for (int k = 0; k < kRd; ++k) {
+            const bool ok = 4 * k + lk < m && li < w;
+            const T v = a.lu[ok ? pos[k] + li : 0];
+            u[k] = ok ? v : T(0);
+        }
+        load_rows(0);
+        // the next group's records
+        const int gn = g1;
+        int npos[kRd], nrelb = 0, ngend = 0;
+        int4 ngeo = geo;
+        if (gn < p1) {
+            ngend = a.pair[2 * gn].w;
+            ngeo = a.pair[2 * gn + 1];
+            nrelb = a.pair[2 * min(gn + li, p1 - 1)].z;
+#pragma unroll
+            for (int k = 0; k < kRd; ++k) npos[k] = a.pair[2 * min(gn + 4 * k + lk, p1 - 1)].y;
+        }
+        // unit lower solve U(S, t) = L_SS^-1 A(S, t), four targets to a round, one per row of 16
+        // lanes
+#pragma unroll
+        for (int j = 0; j + 1 < kMedW; ++j) {
+            if (j + 1 < w) {
+#pragma unroll
+                for (int k = 0; k < kRd; ++k)
+                    if (4 * k < m) u[k] = fma(-lc[j], group_bcast<16>(u[k], j), u[k]);
+            }
+        }
+        load_cur();
+#pragma unroll
+        for (int k = 0; k < kRd; ++k) {
+            if (4 * k + lk < m && li < w) a.lu[pos[k] + li] = u[k];
+            L.Ub[(4 * k + lk) * kUbLd + li] = u[k];
+        }
+        wave_order();
+        T bv[kKs];
+#pragma unroll
+        for (int s = 0; s < kKs; ++s) bv[s] = li < m ? L.Ub[li * kUbLd + 4 * s + lk] : T(0);
+        for (int i0 = 0; i0 < r; i0 += 16 * kTl) {
+            if (i0 > 0) {
+                load_rows(i0);
+                load_cur();
+            }
+            typename MM::acc_t acc[kTl];
+#pragma unroll
+            for (int t = 0; t < kTl; ++t) acc[t] = typename MM::acc_t{T(0), T(0), T(0), T(0)};
+#pragma unroll
+            for (int s = 0; s < kKs; ++s)
+                if (4 * s < w) {
+#pragma unroll
+                    for (int t = 0; t < kTl; ++t) acc[t] = MM::step(av[t][s], bv[s], acc[t]);
+                }
+#pragma unroll
+            for (int t = 0; t < kTl; ++t)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (q[t][v] >= 0) a.lu[q[t][v]] = cur[t][v] - acc[t][v];
+        }
+        wave_order();   // the updated targets are read by the next groups and the factorization
+        g0 = gn;
+        if (g0 < p1) {
+            gend = ngend;
+            relb = nrelb;
+            geo = ngeo;
+#pragma unroll
+            for (int k = 0; k < kRd; ++k) pos[k] = npos[k];
+            load_diag();
+        }
+    }
+    if (ia.x >= 0) {
+        const int w = __builtin_amdgcn_readfirstlane(ib.y), nrow = w + __builtin_amdgcn_readfirstlane(ib.z);
+        const int np = w > 8 ? wave_factor<16>(a, w, nrow, sgl, L.Us, thresh)
+                             : wave_factor<8>(a, w, nrow, sgl, L.Us, thresh);
+        if (np && lane == 0) atomicAdd(&a.pcount[slot % kCountSlots], (unsigned long long)np);
+    }
+}
+
 // One launch per level: block b < nwide runs wide item item0 + b; the next f.nsolve blocks
 // run the forward-solve items f.j0 .. f.j1 - 1 (one forward level; they read only columns and
 // unknowns final before the launch), ahead of the narrow items so that they start beside the
@@ -1312,6 +1718,7 @@ template <class T> struct FuseArgs {
     int j0, j1, nsolve;
 };
 template <class T> __device__ void fused_forward_block(const FuseArgs<T> &f, int blk, char *sm);
+constexpr size_t kSolveLdsBytes = 9728;   // of its LDS (SolveLds)
 
 template <class C>
 __device__ __forceinline__ void refactor_block(int blk, int nblk, int item0, const RefArgs<typename C::T> &a,
@@ -1329,11 +1736,52 @@ __device__ __forceinline__ void refactor_block(int blk, int nblk, int item0, con
     }
     if (blk >= nwide) {
         const int b = blk - nwide - f.nsolve;
-        small_group<typename C::T, (C::kMaxW > 16)>(small0, nsmall, a, b * (C::kThreads / 16) + (threadIdx.x >> 4),
+        small_group<typename C::T, (C::kMaxW > 16), false>(small0, nsmall, a, b * (C::kThreads / 16) + (threadIdx.x >> 4),
                                                     b * (C::kThreads / 64) + (threadIdx.x >> 6));
         return;
     }
     wide_item<C>(item0 + blk, a, sm);
+}
+
+// A level whose wide items are all medium, on wavefronts: the first blocks run its nmed medium
+// items, four to a block, the next ones forward-solve items, narrow items (16 lanes each), tiny
+// items (4 lanes each) and the copy, as in refactor_block.
+// kMany: the level has more narrow items than the device holds at once, which skip the loads of
+// idle lanes.
+// Bound by the latency of an item's dependent rounds (record, operands, target values, panel) and
+// of its code.  Against 256-thread blocks with LDS staging: levels of the 200-bus grid 9 -> 6 us,
+// of 2,000 buses 13.1 -> 10.6 us, of 70,000 buses with fewer than 16,384 narrow items 25-33 ->
+// 17-22 us.
+template <class T, bool kMany>
+__global__ __launch_bounds__(256, 3) void k_refactor_wave(int item0, RefArgs<T> a, int nmed, int small0, int nsmall,
+                                                          int ntiny, CopyRanges c, FuseArgs<T> f) {
+    __shared__ __align__(16) char sm[sizeof(WaveLds<T>) * 4 > kSolveLdsBytes ? sizeof(WaveLds<T>) * 4 : kSolveLdsBytes];
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nmb = (nmed + 3) / 4, nn = nsmall - ntiny;
+    const int nsb = (nn + kBlock / 16 - 1) / (kBlock / 16), ntb = (ntiny + kBlock / kTinyLanes - 1) / (kBlock / kTinyLanes);
+    int b = blockIdx.x;
+    if (b < nmb) {
+        const int i = b * 4 + wv;
+        if (i < nmed) wave_item<T>(item0 + i, a, reinterpret_cast<WaveLds<T> *>(sm)[wv], i);
+        return;
+    }
+    b -= nmb;
+    if (b < f.nsolve) {
+        fused_forward_block(f, b, sm);
+        return;
+    }
+    b -= f.nsolve;
+    if (b < nsb) {
+        small_group<T, true, kMany>(small0, nn, a, b * (kBlock / 16) + (threadIdx.x >> 4), b * 4 + wv);
+        return;
+    }
+    b -= nsb;
+    if (b < ntb) {
+        small_group<T, true, kMany, kTinyLanes>(small0 + nn, ntiny, a, b * (kBlock / kTinyLanes) + (threadIdx.x / kTinyLanes),
+                                         b * 4 + wv);
+        return;
+    }
+    copy_block(a, c, b - ntb, gridDim.x - nmb - f.nsolve - nsb - ntb, kBlock);
 }
 
 template <class C>
@@ -1462,35 +1910,72 @@ __device__ __forceinline__ double sdot(const SolveArgs<TF> &a, const double *v, 
         const int rem = (q1 - q + width - 1) / width;
         int cc[B];
         double ll[B], vv[B];
+        // entries past the row's end repeat the lane's first one with a zero factor; the second
+        // half of a batch of eight runs if any lane of the wavefront has entries there
+        const bool more = B > 4 && __any(rem > 4);
+        auto load = [&](int k) {
+            const int i = k < rem ? q + k * width : q;
+            cc[k] = a.col[i];
+            ll[k] = (double)a.lucsr[i];
+        };
 #pragma unroll
-        for (int k = 0; k < B; ++k) {
-            const bool h = k < rem;
-            cc[k] = h ? a.col[q + k * width] : 0;
-            ll[k] = h ? (double)a.lucsr[q + k * width] : 0.0;
+        for (int k = 0; k < 4; ++k) load(k);
+        if (more) {
+#pragma unroll
+            for (int k = 4; k < B; ++k) load(k);
+        } else {
+#pragma unroll
+            for (int k = 4; k < B; ++k) {
+                cc[k] = cc[0];
+                ll[k] = 0.0;
+            }
         }
+#pragma unroll
+        for (int k = 1; k < B; ++k) ll[k] = k < rem ? ll[k] : 0.0;
         if constexpr (kWait) {
             unsigned long long bb[B];
 #pragma unroll
-            for (int k = 0; k < B; ++k) bb[k] = k < rem ? load_coherent(v + cc[k]) : 0ULL;
+            for (int k = 0; k < 4; ++k) bb[k] = load_coherent(v + cc[k]);
+            if (more) {
+#pragma unroll
+                for (int k = 4; k < B; ++k) bb[k] = load_coherent(v + cc[k]);
+            } else {
+#pragma unroll
+                for (int k = 4; k < B; ++k) bb[k] = 0ULL;
+            }
+#pragma unroll
+            for (int k = 1; k < B; ++k) bb[k] = k < rem ? bb[k] : 0ULL;   // not polled twice
             wait_batch<B>(bb, v, cc, a.abort);
 #pragma unroll
             for (int k = 0; k < B; ++k) vv[k] = __longlong_as_double((long long)bb[k]);
         } else {
 #pragma unroll
-            for (int k = 0; k < B; ++k) vv[k] = k < rem ? v[cc[k]] : 0.0;
+            for (int k = 0; k < 4; ++k) vv[k] = v[cc[k]];
+            if (more) {
+#pragma unroll
+                for (int k = 4; k < B; ++k) vv[k] = v[cc[k]];
+            } else {
+#pragma unroll
+                for (int k = 4; k < B; ++k) vv[k] = 0.0;
+            }
         }
 #pragma unroll
         for (int k0 = 0; k0 < B; k0 += 4) {
-            const int r4 = rem - k0;
-            if (r4 >= 4) {
+            if (k0 == 0 || more) {
+                const bool full = rem - k0 >= 4;
                 s0 = fma(ll[k0], vv[k0], s0);
-                s1 = fma(ll[k0 + 1], vv[k0 + 1], s1);
-                s2 = fma(ll[k0 + 2], vv[k0 + 2], s2);
-                s3 = fma(ll[k0 + 3], vv[k0 + 3], s3);
-            } else {
-#pragma unroll
-                for (int k = 0; k < 3; ++k)
-                    if (k < r4) s0 = fma(ll[k0 + k], vv[k0 + k], s0);
+                if (__any(full)) {
+                    const double t1 = fma(ll[k0 + 1], vv[k0 + 1], full ? s1 : s0);
+                    s1 = full ? t1 : s1;
+                    s0 = full ? s0 : t1;
+                    const double t2 = fma(ll[k0 + 2], vv[k0 + 2], full ? s2 : s0);
+                    s2 = full ? t2 : s2;
+                    s0 = full ? s0 : t2;
+                    s3 = full ? fma(ll[k0 + 3], vv[k0 + 3], s3) : s3;
+                } else {
+                    s0 = fma(ll[k0 + 1], vv[k0 + 1], s0);
+                    s0 = fma(ll[k0 + 2], vv[k0 + 2], s0);
+                }
             }
         }
     }
@@ -1545,7 +2030,7 @@ __device__ __forceinline__ void lsolve_item(const SolveArgs<TF> &a, int item, do
         const bool lead = rr.x >= 0 && gl == 0;
         double bv = 0.0, Lp[kPackW - 1];
 #pragma unroll
-        for (int k = 0; k < kPackW - 1; ++k) Lp[k] = lead && k < t ? (double)a.lucsr[rr.z + k] : 0.0;
+        for (int k = 0; k < kPackW - 1; ++k) Lp[k] = (double)load_if(a.lucsr, rr.z + k, lead && k < t);
         if (lead) bv = a.bp[rr.x];
         const double acc = sdot<kWait, 4>(a, a.y, rr.y, rr.z, gl, lanes);
         double yv = bv - acc;
@@ -1616,7 +2101,7 @@ __device__ __forceinline__ void usolve_item(const SolveArgs<TF> &a, int item, do
         int qi = 0;
         const int d = rr.y - (w - t);                   // diagonal slot
 #pragma unroll
-        for (int k = 0; k < kPackW - 1; ++k) Up[k] = lead && k < e ? (double)a.lucsr[d + 1 + k] : 0.0;
+        for (int k = 0; k < kPackW - 1; ++k) Up[k] = (double)load_if(a.lucsr, d + 1 + k, lead && k < e);
         if (lead) {
             yv = a.y[rr.x];
             dd = (double)a.lucsr[d];
@@ -1730,6 +2215,7 @@ struct SolveLds {
     double blk[kPanelMax * kRowLd];
 };
 static_assert(offsetof(SolveLds, blk) % 16 == 0, "the staged panel is read in 16-byte pairs");
+static_assert(sizeof(SolveLds) <= kSolveLdsBytes, "LDS of the forward items in a refactorization launch");
 
 constexpr int kPersThreads = kBlock + 64;   // threads of the persistent solves' blocks
 

@@ -49,6 +49,13 @@ constexpr int kNormRowBlocks = 4096;   // most blocks of the row-norm pass (8 la
 // narrow items per level up to which the pipelined variant runs (a tiny item counts a quarter:
 // its 4-lane group keeps four times as many items in flight)
 constexpr int kSmallPipeMax = 100000;
+// narrow items of a level from which idle lanes skip their loads (16,384 groups of 16 lanes
+// exceed the 12 wavefronts a compute unit holds: the memory pipeline, not latency, bounds the
+// level; 25,000 buses, 118,000 items: 27 instead of 34 us), and from which a level with medium
+// items runs its tiny ones on 4 lanes (70,000 buses, 116,000 items: 105 instead of 126 us; 600 to
+// 1,700 items: 18 instead of 14.5 us, their longer code costs more than the room they save)
+constexpr int kManyItems = 16384;
+constexpr int kTinyMinItems = 65536;
 constexpr int kNormBlocks = 4096;
 constexpr int kMaxSweeps = 1024;       // largest approx_sweeps accepted
 constexpr int kMaxRestart = 64;
@@ -125,7 +132,7 @@ void carve(const kkt_handle *h, char *base, Dev &d, size_t *bytes) {
     d.ulen = c.take<int32_t>(n);
     d.pan_start = c.take<int32_t>(g.pan_start.size());
     d.pan_r = c.take<int32_t>(g.pan_r.size());
-    d.itemrec = c.take<int4>(std::max<size_t>(3, g.itemrec.size() / 4));
+    d.itemrec = c.take<int4>(std::max<size_t>(4, g.itemrec.size() / 4));
     d.pair8 = c.take<int4>(std::max<size_t>(2, g.pair8.size() / 4));
     d.ldiag = c.take<int32_t>(n);
     d.f_rel = c.take<int32_t>(std::max<size_t>(1, g.f_rel.size()));
@@ -442,7 +449,7 @@ int enqueue_levels_t(kkt_handle *h, hipStream_t s, bool fused) {
             // the last launch
             const CopyRanges c{fused ? g.copy_lat[copied] : 0, fused ? g.copy_lat[l] : 0, 0, 0};
             if (fused) copied = l;
-            const int nt = g.f_ntiny[l];
+            const int nt = ns >= kManyItems ? g.f_ntiny[l] : 0;
             const int grid = narrow_blocks(ns, nt, kBlock) + copy_blocks(h, copy_count(c), kBlock);
             // many items: keep more in flight; few: shorten each item's dependent chain (only
             // items that pull have one; a level of leaves keeps the plain variant's occupancy)
@@ -450,9 +457,11 @@ int enqueue_levels_t(kkt_handle *h, hipStream_t s, bool fused) {
             const bool pipe = pulls && (ns - nt) + (nt + kTinyLanes - 1) / kTinyLanes <= kSmallPipeMax;
             timed(h, KKT_PROF_REFACTOR_SMALL, s, [&] {
                 if (!pipe)
-                    k_refactor_small<T, false><<<grid, kBlock, 0, s>>>(i0, ns, nt, a, c);
+                    k_refactor_small<T, false, true><<<grid, kBlock, 0, s>>>(i0, ns, nt, a, c);
+                else if (ns >= kManyItems)
+                    k_refactor_small<T, true, true><<<grid, kBlock, 0, s>>>(i0, ns, nt, a, c);
                 else
-                    k_refactor_small<T, true><<<grid, kBlock, 0, s>>>(i0, ns, nt, a, c);
+                    k_refactor_small<T, true, false><<<grid, kBlock, 0, s>>>(i0, ns, nt, a, c);
             }, true);
         }
         if (!nb && !nm) continue;
@@ -482,6 +491,7 @@ int enqueue_levels_t(kkt_handle *h, hipStream_t s, bool fused) {
                 }
             }
         }
+        const bool wave = g.f_wave[l] && a.use_mfma;   // medium items on wavefronts (matrix-core updates only)
         const int threads = nb ? (g.f_w256[l] ? W256::kThreads : Big::kThreads) : Med::kThreads;
         const int cb = copy_blocks(h, copy_count(c), threads);
         if (nb && g.f_w256[l])
@@ -493,6 +503,14 @@ int enqueue_levels_t(kkt_handle *h, hipStream_t s, bool fused) {
             timed(h, KKT_PROF_REFACTOR_LARGE, s, [&] {
                 const int grid = nb + (int)blocks_for(mb, Big::kThreads / 16) + f.nsolve + cb;
                 k_refactor_wide<Big><<<grid, Big::kThreads, Big::kLds, s>>>(i0, a, nb, s0, mb, c, f);
+            }, true);
+        else if (wave)
+            timed(h, KKT_PROF_REFACTOR_MEDIUM, s, [&] {
+                const bool many = ns >= kManyItems;
+                const int nt = ns >= kTinyMinItems ? g.f_ntiny[l] : 0;
+                const int grid = (int)blocks_for(nm, 4) + f.nsolve + narrow_blocks(ns, nt, kBlock) + cb;
+                if (many) k_refactor_wave<T, true><<<grid, kBlock, 0, s>>>(i0, a, nm, s0, ns, nt, c, f);
+                else k_refactor_wave<T, false><<<grid, kBlock, 0, s>>>(i0, a, nm, s0, ns, nt, c, f);
             }, true);
         else
             timed(h, KKT_PROF_REFACTOR_MEDIUM, s, [&] {

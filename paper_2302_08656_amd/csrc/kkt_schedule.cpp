@@ -180,6 +180,7 @@ int build_schedule(const Symbolic &s, const SchedParams &prm, Schedule &g) {
     g.f_nmed.clear();
     g.f_ntiny.clear();
     g.f_w256.clear();
+    g.f_wave.clear();
     g.f_item_panel.clear();
     g.f_item_npan.clear();
     g.f_item_pair.assign(1, 0);
@@ -228,9 +229,19 @@ int build_schedule(const Symbolic &s, const SchedParams &prm, Schedule &g) {
             q = q1;
         }
         std::sort(single.begin(), single.end());
+        // the medium configuration only where a level has no item that needs a bigger one (one
+        // launch per level for the wide items); on one wavefront its items pull at most kWaveGroup
+        // targets together
+        bool any_big = false;
+        for (int32_t T : panels_at[l]) any_big |= pw(T) > kMedW || pw(T) + g.pan_r[T] > kMedRows || gsize[T] > 1;
+        for (const auto &pr : pl) any_big |= pw(pr.second) > kMedW;
+        bool wave = !any_big;
+        for (int32_t T : panels_at[l]) wave &= is_small(T) || pw(T) + g.pan_r[T] <= kWaveRows;
+        for (const auto &pr : pl) wave &= g.pan_r[pr.second] <= kWaveRows;
+        const size_t wide_cap = !wave ? (size_t)prm.group : (size_t)std::min<int32_t>(prm.group, kWaveGroup);
         for (size_t q = 0; q < single.size();) {
             const int32_t S = single[q].first;
-            const size_t cap = is_small(S) ? 1 : (size_t)prm.group;
+            const size_t cap = is_small(S) ? 1 : wide_cap;
             Item it{-1, {}, true, 0.0};
             size_t q1 = q;
             while (q1 < single.size() && single[q1].first == S && q1 - q < cap) it.pairs.push_back(single[q1++]);
@@ -239,36 +250,27 @@ int build_schedule(const Symbolic &s, const SchedParams &prm, Schedule &g) {
         }
         for (auto &it : items) {
             std::sort(it.pairs.begin(), it.pairs.end());
-            int32_t mw = it.panel >= 0 ? pw(it.panel) : 0;
             bool tiny = it.small && (it.panel < 0 || is_tiny(it.panel));
             for (const auto &pr : it.pairs) {
                 if (!is_small(pr.first)) it.small = false;
                 if (!is_tiny(pr.first)) tiny = false;
                 it.cost += (double)pw(pr.first) * (pw(pr.first) + g.pan_r[pr.first]);
-                mw = std::max(mw, pw(pr.first));
             }
             for (int32_t t = 0; t < (it.panel >= 0 ? it.npan : 0); ++t) {
                 const int32_t P = it.panel + t;
                 it.cost += (double)pw(P) * pw(P) * (pw(P) + g.pan_r[P]);
             }
-            const bool fits_med =
-                mw <= kMedW && (it.panel < 0 || pw(it.panel) + g.pan_r[it.panel] <= kMedRows) && it.npan == 1;
-            it.kind = it.small ? (tiny ? 3 : 2) : fits_med ? 1 : 0;
+            it.kind = it.small ? (tiny ? 3 : 2) : any_big ? 0 : 1;
         }
-        // the medium configuration only where a level has no item that needs the big one
-        // (one launch per level for the wide items)
-        bool any_big = false, fit256 = true;
+        bool fit256 = true;
         int32_t nbig = 0;
         for (const auto &it : items) {
-            any_big |= it.kind == 0;
-            nbig += it.kind == 0 || it.kind == 1;
+            nbig += it.kind == 0;
             if (it.kind == 0 && it.panel >= 0 && (pw(it.panel) + g.pan_r[it.panel] > kW256Rows || it.npan > 1))
                 fit256 = false;
         }
-        if (any_big)
-            for (auto &it : items)
-                if (it.kind == 1) it.kind = 0;
-        g.f_w256.push_back(any_big && fit256 && nbig >= kW256MinItems && prm.wide256 ? 1 : 0);
+        g.f_wave.push_back(0);   // set below, on levels with medium items
+        g.f_w256.push_back(nbig >= kW256MinItems && fit256 && prm.wide256 ? 1 : 0);
         for (int32_t T : panels_at[l])
             for (int32_t t = 0; t < gsize[T]; ++t) fac_index[T + t] = -1;
         std::stable_sort(items.begin(), items.end(), [](const Item &a, const Item &b) {
@@ -306,6 +308,7 @@ int build_schedule(const Symbolic &s, const SchedParams &prm, Schedule &g) {
         }
         g.f_nlarge.push_back(nlarge);
         g.f_nmed.push_back(nmed);
+        g.f_wave.back() = nmed > 0 && wave ? 1 : 0;
         g.f_ntiny.push_back(ntiny);
         g.f_lvl.push_back((int32_t)g.f_item_panel.size());
     }
@@ -324,9 +327,9 @@ int build_schedule(const Symbolic &s, const SchedParams &prm, Schedule &g) {
         o[3] = P >= 0 ? g.ldiag[g.pan_start[P]] : 0;
     };
     const size_t nitems = g.f_item_panel.size();
-    g.itemrec.resize(12 * nitems);
+    g.itemrec.assign(16 * nitems, 0);
     for (size_t i = 0; i < nitems; ++i) {
-        int32_t *o = &g.itemrec[12 * i];
+        int32_t *o = &g.itemrec[16 * i];
         o[0] = g.f_item_panel[i];
         o[1] = g.f_item_pair[i];
         o[2] = g.f_item_pair[i + 1];
@@ -347,10 +350,10 @@ int build_schedule(const Symbolic &s, const SchedParams &prm, Schedule &g) {
         for (int32_t it = g.f_lvl[l] + g.f_nlarge[l]; it < g.f_lvl[l + 1]; ++it)
             for (int32_t q = g.f_item_pair[it]; q < g.f_item_pair[it + 1]; ++q) narrow_pair[q] = 1;
         for (int32_t it = g.f_lvl[l]; it < g.f_lvl[l] + g.f_nlarge[l]; ++it) {
-            const int32_t q1 = g.f_item_pair[it + 1];
+            const int32_t q1 = g.f_item_pair[it + 1], cap = g.f_wave[l] ? kWaveGroup : kGroup;
             for (int32_t g0 = g.f_item_pair[it], g1; g0 < q1; g0 = g1) {
                 g1 = g0 + 1;
-                while (g1 < q1 && g.f_pair_src[g1] == g.f_pair_src[g0] && g1 - g0 < kGroup) ++g1;
+                while (g1 < q1 && g.f_pair_src[g1] == g.f_pair_src[g0] && g1 - g0 < cap) ++g1;
                 for (int32_t q = g0; q < g1; ++q) group_end[q] = g1;
             }
         }
@@ -371,6 +374,12 @@ int build_schedule(const Symbolic &s, const SchedParams &prm, Schedule &g) {
             o[0] = S;
             o[3] = group_end[q];
         }
+    }
+    // narrow items carry their first pair's record
+    for (size_t i = 0; i < nitems; ++i) {
+        const size_t q = (size_t)g.f_item_pair[i];
+        if (g.f_item_pair[i] < g.f_item_pair[i + 1] && narrow_pair[q])
+            std::copy(&g.pair8[8 * q], &g.pair8[8 * q] + 8, &g.itemrec[16 * i + 8]);
     }
     // solve levels
     std::vector<int32_t> llev(np, 0), ulev(np, 0);
