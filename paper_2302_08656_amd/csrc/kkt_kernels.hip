@@ -467,9 +467,10 @@ __device__ __forceinline__ void max_parts_body(int nblk, int nfield, const doubl
     }
 }
 
+// one block per column of parts
 __global__ __launch_bounds__(256) void k_max_parts(int nblk, int nfield, const double *__restrict__ part,
                                                    double *__restrict__ dst) {
-    max_parts_body(nblk, nfield, part, dst);
+    max_parts_body(nblk, nfield, part + blockIdx.x * nblk * nfield, dst + blockIdx.x * nfield);
 }
 
 // st->perturbed = sum of the spread counter slots
@@ -1828,6 +1829,11 @@ struct SolveArgs {
     double *usum;         // backward: partial sums of the early U columns of helped rows
     int *abort;           // persistent mode: raised by a wait that timed out
     int *tick;            // persistent mode: next item to take
+    // several columns at once (persistent mode): column c > 0 keeps bp, y, xt, psum, usum in ext,
+    // five vectors of n each, and its solution at x + c ld
+    double *ext;
+    int64_t ld;
+    int n, ncol;
 };
 
 constexpr unsigned long long kUnset = 0x7ff4dead0badf00dULL;   // signaling NaN
@@ -2217,19 +2223,53 @@ struct SolveLds {
 static_assert(offsetof(SolveLds, blk) % 16 == 0, "the staged panel is read in 16-byte pairs");
 static_assert(sizeof(SolveLds) <= kSolveLdsBytes, "LDS of the forward items in a refactorization launch");
 
+// kMulti: a.ncol right-hand sides in one launch, each item once per column, the columns of an
+// item on consecutive tickets.  The chain of levels, not the work, bounds a solve, so columns
+// beside each other cost little more than one (25,000 buses, two columns: 639 -> 398 us; each
+// column's result is the one it gets alone).
 constexpr int kPersThreads = kBlock + 64;   // threads of the persistent solves' blocks
 
+// the buffers of column c > 0
+struct ColumnBufs {
+    double *bp, *y, *xt, *psum, *usum;
+};
+__device__ __forceinline__ ColumnBufs column_bufs(double *ext, int n, int c) {
+    double *e = ext + (int64_t)(5 * (c - 1)) * n;
+    return ColumnBufs{e, e + n, e + 2 * (int64_t)n, e + 3 * (int64_t)n, e + 4 * (int64_t)n};
+}
+
 template <bool kFwd, class TF>
+__device__ __forceinline__ void solve_item(const SolveArgs<TF> &a, int item, SolveLds &L) {
+    if constexpr (kFwd) lsolve_item<true>(a, item, L.ext, L.blk, L.ys);
+    else usolve_item<true>(a, item, L.ext, L.blk);
+}
+
+template <bool kFwd, bool kMulti, class TF>
 __device__ __forceinline__ void persistent_items(int i0, int i1, const SolveArgs<TF> &a) {
     __shared__ SolveLds L;
+    const int total = kMulti ? (i1 - i0) * a.ncol : i1 - i0;
     if (threadIdx.x == kBlock) L.next[0] = atomicAdd(a.tick, 1);
     __syncthreads();
     int cur = L.next[0];
-    for (int par = 1; i0 + cur < i1; par ^= 1) {
+    for (int par = 1; cur < total; par ^= 1) {
         int nt = 0;
         if (threadIdx.x == kBlock) nt = atomicAdd(a.tick, 1);
-        if constexpr (kFwd) lsolve_item<true>(a, i0 + cur, L.ext, L.blk, L.ys);
-        else usolve_item<true>(a, i0 + cur, L.ext, L.blk);
+        if constexpr (kMulti) {
+            const int t = __builtin_amdgcn_readfirstlane(cur), col = t % a.ncol;
+            SolveArgs<TF> b = a;
+            if (col) {
+                const ColumnBufs e = column_bufs(a.ext, a.n, col);
+                b.bp = e.bp;
+                b.y = e.y;
+                b.xt = e.xt;
+                b.psum = e.psum;
+                b.usum = e.usum;
+                b.x = a.x + col * a.ld;
+            }
+            solve_item<kFwd>(b, i0 + t / a.ncol, L);
+        } else {
+            solve_item<kFwd>(a, i0 + cur, L);
+        }
         // the slot was last read two barriers ago
         if (threadIdx.x == kBlock) L.next[par] = nt;
         __syncthreads();
@@ -2237,15 +2277,15 @@ __device__ __forceinline__ void persistent_items(int i0, int i1, const SolveArgs
     }
 }
 
-template <class TF>
+template <class TF, bool kMulti = false>
 __global__ __launch_bounds__(kPersThreads) void k_lsolve_persistent(int i0, int i1, SolveArgs<TF> a) {
-    persistent_items<true>(i0, i1, a);
+    persistent_items<true, kMulti>(i0, i1, a);
 }
 
-template <class TF>
+template <class TF, bool kMulti = false>
 __global__ __launch_bounds__(kPersThreads) void k_usolve_persistent(int i0, int i1, SolveArgs<TF> a) {
     if (!a.x) a.x = call_x(a.call);
-    persistent_items<false>(i0, i1, a);
+    persistent_items<false, kMulti>(i0, i1, a);
 }
 
 // Block blk of the f.nsolve extra blocks of a refactorization launch that run the items of
@@ -2287,6 +2327,16 @@ __global__ void k_solve_reset(int n, const double *__restrict__ b0, const CallPt
                               double *__restrict__ usum, int mark, int ntick, int *__restrict__ tick) {
     const double *__restrict__ b = b0 ? b0 : call_ptr(&call->b);   // b0 null: the recorded call's
     solve_reset_body(blockIdx.x * blockDim.x + threadIdx.x, n, b, r, P, bp, y, xt, psum, usum, mark, ntick, tick);
+}
+
+// The set-up of gridDim.y columns (b at b + c ld; buffers as in SolveArgs), unknowns marked unset
+__global__ void k_solve_reset_cols(int n, const double *__restrict__ b, int64_t ld, const double *__restrict__ r,
+                                   const int32_t *__restrict__ P, double *bp, double *y, double *xt, double *psum,
+                                   double *usum, double *ext, int *__restrict__ tick) {
+    const int c = blockIdx.y, i = blockIdx.x * blockDim.x + threadIdx.x;
+    ColumnBufs e{bp, y, xt, psum, usum};
+    if (c) e = column_bufs(ext, n, c);
+    solve_reset_body(i, n, b + c * ld, r, P, e.bp, e.y, e.xt, e.psum, e.usum, 1, c ? 0 : 2, tick);
 }
 
 // The column pass of the value update with the solve's set-up for the recorded call's
@@ -2441,15 +2491,17 @@ __global__ __launch_bounds__(256) void k_unpermute(int n, const int32_t *__restr
 
 // res = b - A x (8 lanes per row, kRowsPerGroup rows per group, grid-stride) and block
 // maxima of |res|, |x|, |b| into part[3 * block + {0, 1, 2}]; v0, x0, b0 null: those of the
-// recorded call
+// recorded call.  Column blockIdx.y: x and b at + ld, block maxima after the other columns'; res
+// null: maxima only
 __global__ __launch_bounds__(256) void k_residual(int n, const int32_t *__restrict__ rowptr,
                                                   const int32_t *__restrict__ col, const double *v0,
-                                                  const double *x0, const double *b0, const CallPtrs *call,
-                                                  double *__restrict__ res, double *__restrict__ part) {
+                                                  const double *x0, const double *b0, int64_t ld,
+                                                  const CallPtrs *call, double *__restrict__ res,
+                                                  double *__restrict__ part) {
     __shared__ double red[3][4];
     const double *__restrict__ v = v0 ? v0 : call_ptr(&call->v);
-    const double *__restrict__ x = x0 ? x0 : call_x(call);
-    const double *__restrict__ b = b0 ? b0 : call_ptr(&call->b);
+    const double *__restrict__ x = x0 ? x0 + blockIdx.y * ld : call_x(call);
+    const double *__restrict__ b = b0 ? b0 + blockIdx.y * ld : call_ptr(&call->b);
     const double qnan = __longlong_as_double(0x7ff8000000000000LL);
     double rn = 0.0, xn = 0.0, bn = 0.0;
     const int gl = threadIdx.x & 7;
@@ -2476,7 +2528,7 @@ __global__ __launch_bounds__(256) void k_residual(int n, const int32_t *__restri
             const int i = i0 + k;
             if (gl == 0 && i < n) {
                 const double ri = b[i] - sk;
-                res[i] = ri;
+                if (res) res[i] = ri;
                 rn = isnan(ri) ? qnan : fmax(rn, fabs(ri));
                 xn = isnan(x[i]) ? qnan : fmax(xn, fabs(x[i]));
                 bn = fmax(bn, fabs(b[i]));
@@ -2501,7 +2553,7 @@ __global__ __launch_bounds__(256) void k_residual(int n, const int32_t *__restri
             const double y = red[threadIdx.x][q];
             t = (isnan(t) || isnan(y)) ? t + y : fmax(t, y);
         }
-        part[3 * blockIdx.x + threadIdx.x] = t;
+        part[3 * (blockIdx.y * gridDim.x + blockIdx.x) + threadIdx.x] = t;
     }
 }
 

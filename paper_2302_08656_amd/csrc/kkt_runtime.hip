@@ -59,6 +59,7 @@ constexpr int kTinyMinItems = 65536;
 constexpr int kNormBlocks = 4096;
 constexpr int kMaxSweeps = 1024;       // largest approx_sweeps accepted
 constexpr int kMaxRestart = 64;
+constexpr int kMaxCols = 8;            // most right-hand sides solved by one launch
 
 struct Carver {
     char *base;
@@ -168,7 +169,7 @@ void carve(const kkt_handle *h, char *base, Dev &d, size_t *bytes) {
     d.hbuf = c.take<double>(4 * (size_t)(m + 2));
     d.ybuf = c.take<double>((size_t)m + 2);
     d.st = c.take<DevStatus>(1);
-    d.rn = c.take<ResNorms>(1);
+    d.rn = c.take<ResNorms>(kMaxCols);
     d.tick = c.take<int>(3);
     d.call = c.take<CallPtrs>(1);
     *bytes = c.off + 256;
@@ -301,7 +302,7 @@ int enqueue_solve_t(kkt_handle *h, const double *b, double *x, hipStream_t s, bo
     const int n = h->sym.n;
     const bool pers = h->opts.persistent_solve != 0;
     SolveArgs<TF> a{d.l_item4, d.l_rows4, d.rinfo4, d.csr_col, d.Q, static_cast<const TF *>(d.lucsr), d.c, d.bp, d.y,
-                    d.xt, x, d.call, d.psum, d.usum, &d.st->abort, d.tick};
+                    d.xt, x, d.call, d.psum, d.usum, &d.st->abort, d.tick, nullptr, 0, n, 1};
     if (forward)
         timed(h, KKT_PROF_LSOLVE, s, [&] {
             k_solve_reset<<<blocks_for(n, 256), 256, 0, s>>>(n, b, d.call, d.r, d.P, d.bp, d.y, d.xt, d.psum, d.usum,
@@ -337,6 +338,47 @@ int enqueue_solve_t(kkt_handle *h, const double *b, double *x, hipStream_t s, bo
 
 int enqueue_solve(kkt_handle *h, const double *b, double *x, hipStream_t s, bool forward = true) {
     return by_precision(h, [&](auto tag) { return enqueue_solve_t<decltype(tag)>(h, b, x, s, forward); });
+}
+
+// The columns that one launch per triangle can solve: the buffers of those after the first lie
+// in the Krylov basis V, the residuals' block maxima in Z (both unused until FGMRES steps).
+int solve_cols(const kkt_handle *h, int nrhs) {
+    const int m = h->opts.gmres_restart;
+    if (h->opts.persistent_solve == 0) return 1;
+    const int c = std::min(std::min(nrhs, kMaxCols), 1 + (m + 1) / 5);
+    return (int64_t)3 * norm_blocks(h->sym.n) * c <= (int64_t)m * h->sym.n ? c : 1;
+}
+
+// x_c = Q C (L U)^-1 P R b_c for ncol columns at stride ld, in one launch per triangle
+template <class TF>
+int enqueue_solve_cols_t(kkt_handle *h, const double *b, double *x, int ncol, int64_t ld, hipStream_t s) {
+    const Schedule &g = h->sch;
+    const Dev &d = h->d;
+    const int n = h->sym.n;
+    SolveArgs<TF> a{d.l_item4, d.l_rows4, d.rinfo4, d.csr_col, d.Q, static_cast<const TF *>(d.lucsr), d.c, d.bp, d.y,
+                    d.xt, x, d.call, d.psum, d.usum, &d.st->abort, d.tick, d.V, ld, n, ncol};
+    timed(h, KKT_PROF_LSOLVE, s, [&] {
+        k_solve_reset_cols<<<dim3(blocks_for(n, 256), ncol), 256, 0, s>>>(n, b, ld, d.r, d.P, d.bp, d.y, d.xt, d.psum,
+                                                                         d.usum, d.V, d.tick);
+    });
+    const int nl = g.l_lvl.back(), nu = g.u_lvl.back();
+    timed(h, KKT_PROF_LSOLVE, s, [&] {
+        k_lsolve_persistent<TF, true><<<std::min(nl * ncol, h->grid_l), kPersThreads, 0, s>>>(0, nl, a);
+    });
+    a.item = d.u_item4;
+    a.rows = d.u_rows4;
+    a.rinfo = d.urinfo4;
+    a.tick = d.tick + 1;
+    timed(h, KKT_PROF_USOLVE, s, [&] {
+        k_usolve_persistent<TF, true><<<std::min(nu * ncol, h->grid_u), kPersThreads, 0, s>>>(0, nu, a);
+    });
+    HIPCHK(hipGetLastError());
+    return KKT_OK;
+}
+
+int enqueue_solve_cols(kkt_handle *h, const double *b, double *x, int ncol, int64_t ld, hipStream_t s) {
+    if (ncol == 1) return enqueue_solve(h, b, x, s);
+    return by_precision(h, [&](auto tag) { return enqueue_solve_cols_t<decltype(tag)>(h, b, x, ncol, ld, s); });
 }
 
 // stores the call's values (and right-hand side and solution, or null) for the recorded
@@ -429,7 +471,7 @@ int enqueue_levels_t(kkt_handle *h, hipStream_t s, bool fused) {
     const int u0 = g.copy_uat[0], nup = (int)g.copy_k.size() - u0, ntop = nlev - g.copy_lvl;
     int ucopied = u0, ktop = 0;
     const SolveArgs<T> fs{d.l_item4, d.l_rows4, d.rinfo4, d.csr_col, d.Q, static_cast<const T *>(d.lucsr), d.c,
-                          d.bp, d.y, d.xt, nullptr, d.call, d.psum, d.usum, &d.st->abort, d.tick + 2};
+                          d.bp, d.y, d.xt, nullptr, d.call, d.psum, d.usum, &d.st->abort, d.tick + 2, nullptr, 0, h->sym.n, 1};
     const int nfl = (int)g.l_lvl.size() - 1;
     {
         // fused: the column pass also sets up the solve (bp from the stored right-hand side,
@@ -560,31 +602,45 @@ int enqueue_residual(kkt_handle *h, const double *v, const double *x, const doub
     const Dev &d = h->d;
     const int n = h->sym.n, nb = norm_blocks(n);
     timed(h, KKT_PROF_RESIDUAL, s, [&] {
-        k_residual<<<nb, 256, 0, s>>>(n, d.a_rowptr, d.a_colind, v, x, b, d.call, d.res, d.part);
+        k_residual<<<nb, 256, 0, s>>>(n, d.a_rowptr, d.a_colind, v, x, b, 0, d.call, d.res, d.part);
     });
     timed(h, KKT_PROF_RESIDUAL, s, [&] { k_max_parts<<<1, 256, 0, s>>>(nb, 3, d.part, &d.rn->rnorm); });
     HIPCHK(hipGetLastError());
     return KKT_OK;
 }
 
-// berr on the host from the norms of enqueue_residual (and the status block read with them
-// in *sto)
-int residual_berr(kkt_handle *h, double *berr, double *den, hipStream_t s, DevStatus *sto = nullptr) {
+// the norms of ncol columns at stride ld, column c's into d.rn[c]
+int enqueue_residual_cols(kkt_handle *h, const double *x, const double *b, int ncol, int64_t ld, hipStream_t s) {
+    const Dev &d = h->d;
+    const int n = h->sym.n, nb = norm_blocks(n);
+    timed(h, KKT_PROF_RESIDUAL, s, [&] {
+        k_residual<<<dim3(nb, ncol), 256, 0, s>>>(n, d.a_rowptr, d.a_colind, h->d_values, x, b, ld, d.call, nullptr, d.Z);
+    });
+    timed(h, KKT_PROF_RESIDUAL, s, [&] { k_max_parts<<<ncol, 256, 0, s>>>(nb, 3, d.Z, &d.rn->rnorm); });
+    HIPCHK(hipGetLastError());
+    return KKT_OK;
+}
+
+// berr and its denominator of ncol columns on the host from the norms of enqueue_residual
+// (_cols), and the status block read with them in *sto
+int residual_berr(kkt_handle *h, double *berr, double *den, hipStream_t s, DevStatus *sto = nullptr, int ncol = 1) {
     const Dev &d = h->d;
     // the residual norms are carved right after the status block: one read-back takes both
     const size_t off = static_cast<size_t>(reinterpret_cast<const char *>(d.rn) - reinterpret_cast<const char *>(d.st));
-    if (off < sizeof(DevStatus) || off + sizeof(ResNorms) > sizeof(h->h_stage)) return KKT_ERR_DEVICE;
-    HIPCHK(hipMemcpyAsync(h->h_small, d.st, off + sizeof(ResNorms), hipMemcpyDeviceToHost, s));
+    if (off < sizeof(DevStatus) || off + kMaxCols * sizeof(ResNorms) > sizeof(h->h_stage)) return KKT_ERR_DEVICE;
+    HIPCHK(hipMemcpyAsync(h->h_small, d.st, off + ncol * sizeof(ResNorms), hipMemcpyDeviceToHost, s));
     HIPCHK(sync_fold(h, s));
     DevStatus st;
-    ResNorms rn;
     std::memcpy(&st, h->h_small, sizeof(st));
-    std::memcpy(&rn, reinterpret_cast<const char *>(h->h_small) + off, sizeof(rn));
     if (sto) *sto = st;
     if (st.abort) return KKT_ERR_DEVICE;
-    *den = st.anorm * rn.xnorm + rn.bnorm;
-    if (*den == 0.0) *berr = rn.rnorm == 0.0 ? 0.0 : INFINITY;
-    else *berr = rn.rnorm / *den;
+    for (int c = 0; c < ncol; ++c) {
+        ResNorms rn;
+        std::memcpy(&rn, reinterpret_cast<const char *>(h->h_small) + off + c * sizeof(rn), sizeof(rn));
+        den[c] = st.anorm * rn.xnorm + rn.bnorm;
+        if (den[c] == 0.0) berr[c] = rn.rnorm == 0.0 ? 0.0 : INFINITY;
+        else berr[c] = rn.rnorm / den[c];
+    }
     return KKT_OK;
 }
 
@@ -641,16 +697,19 @@ int enqueue_approx_solve(kkt_handle *h, const double *b, double *x, int sweeps, 
     return by_precision(h, [&](auto tag) { return enqueue_approx_solve_t<decltype(tag)>(h, b, x, sweeps, s); });
 }
 
-// FGMRES on one column from the first solve x = M^-1 b.  fused: the refactorization, that
-// solve and its residual were enqueued together; the factorization's status is checked with
-// the first residual (a failed factorization returns its error with info = {0, error, inf,
-// perturbed pivots}, as kkt_refine does).
-int fgmres_column(kkt_handle *h, const double *b, double *x, kkt_info *info, hipStream_t s, bool fused = false) {
+// FGMRES on one column from the first solve x = M^-1 b, which is enqueued here, or was before
+// (kSolved), or together with the refactorization and its residual (kStep): then the
+// factorization's status is checked with the first residual (a failed factorization returns its
+// error with info = {0, error, inf, perturbed pivots}, as kkt_refine does).
+enum FirstSolve { kSolveHere, kSolved, kStep };
+int fgmres_column(kkt_handle *h, const double *b, double *x, kkt_info *info, hipStream_t s,
+                  FirstSolve from = kSolveHere) {
+    const bool fused = from == kStep;
     const Dev &d = h->d;
     const int n = h->sym.n;
     const int m = h->opts.gmres_restart;
     const double tol = h->opts.berr_tol;
-    int rc = fused ? KKT_OK : enqueue_solve(h, b, x, s);
+    int rc = from == kSolveHere ? enqueue_solve(h, b, x, s) : KKT_OK;
     if (rc) return rc;
     int64_t pert = 0;
     std::vector<double> H, cs(m), sn(m), gv(m + 1), yv(m);   // H: made by the first Arnoldi step
@@ -1148,7 +1207,7 @@ int kkt_refactor_refine(kkt_handle *h, const double *d_values, const double *d_b
     h->d_values = d_values;
     h->factored = true;
     kkt_info inf{};
-    rc = fgmres_column(h, b, d_x, &inf, stream, true);
+    rc = fgmres_column(h, b, d_x, &inf, stream, kStep);
     if (info && (rc >= 0 || inf.status < 0)) *info = inf;   // a failed factorization fills inf
     return rc;
 }
@@ -1173,8 +1232,10 @@ int kkt_solve(kkt_handle *h, const double *d_b, double *d_x, int32_t nrhs, int64
     if (!h->factored) return KKT_ERR_STATE;
     DeviceGuard dg(h->device);
     if (!dg.ok) return KKT_ERR_DEVICE;
-    for (int32_t j = 0; j < nrhs; ++j) {
-        const int rc = enqueue_solve(h, d_b + (size_t)j * ld, d_x + (size_t)j * ld, stream);
+    const int nc = solve_cols(h, nrhs);
+    for (int32_t j = 0; j < nrhs; j += nc) {
+        const int rc = enqueue_solve_cols(h, d_b + (size_t)j * ld, d_x + (size_t)j * ld, std::min(nc, nrhs - j), ld,
+                                          stream);
         if (rc) return rc;
     }
     return KKT_OK;
@@ -1212,7 +1273,32 @@ int kkt_refine(kkt_handle *h, const double *d_b, double *d_x, int32_t nrhs, int6
         return fst;
     }
     int worst = KKT_OK;
-    for (int32_t j = 0; j < nrhs; ++j) {
+    // columns beside each other: their first solves and residuals together, then FGMRES column by
+    // column for those short of the target.  Right-hand sides that the solutions overwrite go
+    // one by one through the saved copy.
+    const int nc = d_b == d_x ? 1 : solve_cols(h, nrhs);
+    const int32_t jm = nc > 1 ? nrhs : 0;
+    for (int32_t j0 = 0; j0 < jm; j0 += nc) {
+        const int c1 = std::min(nc, nrhs - j0);
+        const double *b = d_b + (size_t)j0 * ld;
+        double *x = d_x + (size_t)j0 * ld;
+        double berr[kMaxCols], den[kMaxCols];
+        int rc = enqueue_solve_cols(h, b, x, c1, ld, stream);
+        if (!rc) rc = enqueue_residual_cols(h, x, b, c1, ld, stream);
+        if (!rc) rc = residual_berr(h, berr, den, stream, nullptr, c1);
+        if (rc) return rc;
+        for (int c = 0; c < c1; ++c) {
+            kkt_info inf{0, KKT_OK, berr[c], pert};
+            if (!(berr[c] <= h->opts.berr_tol)) {
+                rc = fgmres_column(h, b + (size_t)c * ld, x + (size_t)c * ld, &inf, stream, kSolved);
+                if (rc < 0) return rc;
+                inf.perturbed_pivots = pert;
+                worst = std::max(worst, rc);
+            }
+            if (info) info[j0 + c] = inf;
+        }
+    }
+    for (int32_t j = jm; j < nrhs; ++j) {
         const double *b = d_b + (size_t)j * ld;
         double *x = d_x + (size_t)j * ld;
         if (b == x) {
