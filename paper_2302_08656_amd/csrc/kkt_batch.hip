@@ -5,8 +5,10 @@
 // handle's internals).
 //
 // Each launch is cut into shares, one per handle: share p runs blocks [blk0, blk0 + nblk)
-// of the launch with that handle's arguments, exactly the blocks a launch of the handle
-// alone would run, so every handle's result is bitwise the same as refactoring it alone.
+// of the launch with that handle's arguments, so every handle's result is bitwise the same as
+// refactoring it alone.  The refinement solves all handles' first systems in one launch per
+// triangle, on tickets over an order of their items level by level, and reads all their norms
+// back together; FGMRES follows handle by handle for those short of the target.
 
 namespace kkt {
 
@@ -20,6 +22,22 @@ struct BatchSys {
     int16_t *er, *ec;
     int n, eq, nb_norm;
     CopyRanges rest;   // the copy after the last level
+    // refinement: the two triangles' solves (solutions and right-hand sides come with the call)
+    SolveArgs<T> l, u;
+    const int32_t *P;
+    double *rpart;     // block maxima of the residual
+};
+
+// What the refinement of one handle reads back: its status block and residual norms.
+struct BatchResult {
+    DevStatus st;
+    ResNorms rn;
+};
+
+// The call's pointers of one handle.
+struct BatchPtrs {
+    const double *v, *b;
+    double *x;
 };
 
 // One handle's share of a batched launch.
@@ -90,6 +108,79 @@ __global__ __launch_bounds__(C::kThreads, C::kWaves) void k_batch_level(const Ba
                       FuseArgs<typename C::T>{}, sm);
 }
 
+// A level whose wide items are all medium ones of wavefront levels, in every handle: as
+// k_refactor_wave, with shares
+template <class T, bool kMany>
+__global__ __launch_bounds__(256, 3) void k_batch_wave(const BatchSys<T> *__restrict__ sys,
+                                                       const BatchPart *__restrict__ parts, int nparts) {
+    __shared__ __align__(16) char sm[sizeof(WaveLds<T>) * 4];
+    const BatchPart P = parts[find_part(parts, nparts, blockIdx.x)];
+    const RefArgs<T> a = sys[P.sys].ref;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nmb = (P.nwide + 3) / 4, nsb = (P.nsmall + kBlock / 16 - 1) / (kBlock / 16);
+    const int b = blockIdx.x - P.blk0;
+    if (b < nmb) {
+        const int i = b * 4 + wv;
+        if (i < P.nwide) wave_item<T>(P.item0 + i, a, reinterpret_cast<WaveLds<T> *>(sm)[wv], i);
+    } else if (b < nmb + nsb) {
+        small_group<T, true, kMany>(P.small0, P.nsmall, a, (b - nmb) * (kBlock / 16) + (threadIdx.x >> 4),
+                                    (b - nmb) * 4 + wv);
+    } else {
+        copy_block(a, P.c, b - nmb - nsb, P.nblk - nmb - nsb, kBlock);
+    }
+}
+
+// the solve's set-up of every handle (grid y), unknowns marked unset; the first clears the tickets
+template <class T>
+__global__ __launch_bounds__(256) void k_batch_reset(const BatchSys<T> *__restrict__ sys,
+                                                     const BatchPtrs *__restrict__ ptrs, int *tick) {
+    const BatchSys<T> &S = sys[blockIdx.y];
+    double *bp = const_cast<double *>(S.l.bp);
+    solve_reset_body(blockIdx.x * blockDim.x + threadIdx.x, S.n, ptrs[blockIdx.y].b, S.r, S.P, bp, S.l.y, S.l.xt,
+                     S.l.psum, S.l.usum, 1, blockIdx.y ? 0 : 2, tick);
+}
+
+// One triangle of every handle: blocks take entries of order (handle, item) by ticket
+template <bool kFwd, class T>
+__global__ __launch_bounds__(kPersThreads) void k_batch_solve(const BatchSys<T> *__restrict__ sys,
+                                                              const BatchPtrs *__restrict__ ptrs,
+                                                              const int2 *__restrict__ order, int total, int *tick) {
+    __shared__ SolveLds L;
+    if (threadIdx.x == kBlock) L.next[0] = atomicAdd(tick, 1);
+    __syncthreads();
+    int cur = L.next[0];
+    for (int par = 1; cur < total; par ^= 1) {
+        int nt = 0;
+        if (threadIdx.x == kBlock) nt = atomicAdd(tick, 1);
+        const int2 o = order[__builtin_amdgcn_readfirstlane(cur)];
+        const int q = __builtin_amdgcn_readfirstlane(o.x);
+        SolveArgs<T> a = kFwd ? sys[q].l : sys[q].u;
+        if constexpr (!kFwd) a.x = ptrs[q].x;
+        solve_item<kFwd>(a, __builtin_amdgcn_readfirstlane(o.y), L);
+        if (threadIdx.x == kBlock) L.next[par] = nt;
+        __syncthreads();
+        cur = L.next[par];
+    }
+}
+
+// norms of every handle's residual (grid y; a handle's own number of blocks)
+template <class T>
+__global__ __launch_bounds__(256) void k_batch_residual(const BatchSys<T> *__restrict__ sys,
+                                                        const BatchPtrs *__restrict__ ptrs) {
+    const BatchSys<T> &S = sys[blockIdx.y];
+    if ((int)blockIdx.x >= S.nb_norm) return;
+    const BatchPtrs p = ptrs[blockIdx.y];
+    residual_body(blockIdx.x, S.nb_norm, S.n, S.a_rowptr, S.a_colind, p.v, p.x, p.b, nullptr, S.rpart);
+}
+
+template <class T>
+__global__ __launch_bounds__(256) void k_batch_result(const BatchSys<T> *__restrict__ sys, int norms,
+                                                      BatchResult *__restrict__ out) {
+    const BatchSys<T> &S = sys[blockIdx.x];
+    if (norms) max_parts_body(S.nb_norm, 3, S.rpart, &out[blockIdx.x].rn.rnorm);
+    if (threadIdx.x == 0) out[blockIdx.x].st = *S.ref.st;
+}
+
 // the copy after the last level and the replaced-pivot sums
 template <class T>
 __global__ void k_batch_copy(const BatchSys<T> *__restrict__ sys, const BatchPart *__restrict__ parts, int nparts) {
@@ -120,7 +211,8 @@ struct kkt_batch {
     const double **h_vals = nullptr;   // pinned staging of the value pointers
     hipEvent_t vals_done = nullptr;    // the last upload of h_vals has been read
     // launches of a step: kind (0 clear, 1 rows, 2 cols, 3 scatter, 4 norms, 5 level,
-    // 6 copy, 7 counts), grid, first share, shares
+    // 6 copy, 7 counts, 8 wavefront level, 9 the same with many narrow items), grid, first share,
+    // shares
     struct Launch {
         int kind, grid, p0, np;
     };
@@ -134,6 +226,12 @@ struct kkt_batch {
     // after the caller's stream
     std::vector<hipStream_t> rstreams;
     hipEvent_t ready = nullptr;
+    // merged first solves of the refinement: items of all handles in level order
+    int nl = 0, nu = 0, grid_l = 1, grid_u = 1, nmax = 0, nbmax = 0;
+    int2 *d_lord = nullptr, *d_uord = nullptr;
+    int *d_tick = nullptr;
+    BatchPtrs *d_ptrs = nullptr, *h_ptrs = nullptr;     // device table, its pinned staging
+    BatchResult *d_res = nullptr, *h_res = nullptr;
 };
 
 namespace {
@@ -161,6 +259,14 @@ BatchSys<T> batch_sys(const kkt_handle *h) {
     b.eq = h->opts.equilibrate != 0;
     b.nb_norm = norm_blocks(h->sym.n);
     b.rest = copy_rest(g, copy_carriers(g));
+    b.l = SolveArgs<T>{d.l_item4, d.l_rows4, d.rinfo4, d.csr_col, d.Q, static_cast<const T *>(d.lucsr), d.c, d.bp,
+                       d.y, d.xt, nullptr, d.call, d.psum, d.usum, &d.st->abort, nullptr, nullptr, 0, b.n, 1};
+    b.u = b.l;
+    b.u.item = d.u_item4;
+    b.u.rows = d.u_rows4;
+    b.u.rinfo = d.urinfo4;
+    b.P = d.P;
+    b.rpart = d.part;
     return b;
 }
 
@@ -203,7 +309,17 @@ int batch_build(kkt_batch *b, std::vector<BatchPart> &parts, std::vector<char> &
     int nlev = 0;
     for (auto *h : b->hs) nlev = std::max(nlev, (int)h->sch.f_lvl.size() - 1);
     for (int l = 0; l < nlev; ++l) {
-        add(5, shares([&](int i, BatchPart &p) {
+        // on wavefronts where every handle's level allows it
+        bool wave = true;
+        int64_t narrow = 0;
+        for (auto *h : b->hs) {
+            const Schedule &g = h->sch;
+            if (l + 1 >= (int)g.f_lvl.size()) continue;
+            wave &= h->opts.dense_mfma != 0 && (g.f_wave[l] || g.f_nlarge[l] == 0);
+            narrow += g.f_lvl[l + 1] - g.f_lvl[l] - g.f_nlarge[l];
+        }
+        const int threads = wave ? kBlock : Big::kThreads;
+        add(!wave ? 5 : narrow >= kManyItems ? 9 : 8, shares([&](int i, BatchPart &p) {
             const kkt_handle *h = b->hs[i];
             const Schedule &g = h->sch;
             if (l + 1 >= (int)g.f_lvl.size()) return 0;
@@ -216,7 +332,7 @@ int batch_build(kkt_batch *b, std::vector<BatchPart> &parts, std::vector<char> &
             p.nsmall = ns;
             p.c = copy ? copy_chunk(g, cc, ncopy) : CopyRanges{0, 0, 0, 0};
             const int cb = copy_count(p.c) > 0 ? h->ncu : 0;
-            return nw + (int)blocks_for(ns, Big::kThreads / 16) + cb;
+            return (wave ? (int)blocks_for(nw, 4) : nw) + (int)blocks_for(ns, threads / 16) + cb;
         }));
     }
     add(6, shares([&](int i, BatchPart &) { return (int)blocks_for(copy_count(sys[i].rest), 256); }));
@@ -239,6 +355,8 @@ int batch_enqueue(kkt_batch *b, hipStream_t s) {
             case 5: k_batch_level<Big><<<L.grid, Big::kThreads, Big::kLds, s>>>(sys, p, L.np); break;
             case 6: k_batch_copy<T><<<L.grid, 256, 0, s>>>(sys, p, L.np); break;
             case 7: k_batch_counts<T><<<L.grid, 256, 0, s>>>(sys); break;
+            case 8: k_batch_wave<T, false><<<L.grid, kBlock, 0, s>>>(sys, p, L.np); break;
+            case 9: k_batch_wave<T, true><<<L.grid, kBlock, 0, s>>>(sys, p, L.np); break;
         }
     }
     HIPCHK(hipGetLastError());
@@ -263,8 +381,50 @@ void batch_free(kkt_batch *b) {
         if (b->vals_done) (void)hipEventDestroy(b->vals_done);
         if (b->dmem) (void)hipFree(b->dmem);
         if (b->h_vals) (void)hipHostFree(b->h_vals);
+        if (b->h_ptrs) (void)hipHostFree(b->h_ptrs);
+        if (b->h_res) (void)hipHostFree(b->h_res);
     }
     delete b;
+}
+
+// (handle, item) of every handle's solve items, level by level
+void batch_order(const kkt_batch *b, bool fwd, std::vector<int2> &ord) {
+    size_t nlev = 0;
+    for (auto *h : b->hs) nlev = std::max(nlev, (fwd ? h->sch.l_lvl : h->sch.u_lvl).size() - 1);
+    for (size_t l = 0; l < nlev; ++l)
+        for (size_t q = 0; q < b->hs.size(); ++q) {
+            const std::vector<int32_t> &lvl = fwd ? b->hs[q]->sch.l_lvl : b->hs[q]->sch.u_lvl;
+            if (l + 1 >= lvl.size()) continue;
+            for (int32_t it = lvl[l]; it < lvl[l + 1]; ++it) ord.push_back(int2{(int)q, it});
+        }
+}
+
+template <class T>
+int batch_first_solves_t(kkt_batch *b, hipStream_t s) {
+    const auto *sys = static_cast<const BatchSys<T> *>(b->d_sys);
+    const unsigned cnt = (unsigned)b->hs.size();
+    k_batch_reset<T><<<dim3(blocks_for(b->nmax, 256), cnt), 256, 0, s>>>(sys, b->d_ptrs, b->d_tick);
+    k_batch_solve<true, T><<<std::min(b->nl, b->grid_l), kPersThreads, 0, s>>>(sys, b->d_ptrs, b->d_lord, b->nl,
+                                                                              b->d_tick);
+    k_batch_solve<false, T><<<std::min(b->nu, b->grid_u), kPersThreads, 0, s>>>(sys, b->d_ptrs, b->d_uord, b->nu,
+                                                                               b->d_tick + 1);
+    k_batch_residual<T><<<dim3(b->nbmax, cnt), 256, 0, s>>>(sys, b->d_ptrs);
+    k_batch_result<T><<<cnt, 256, 0, s>>>(sys, 1, b->d_res);
+    HIPCHK(hipGetLastError());
+    return KKT_OK;
+}
+
+// the handles' status blocks (and residual norms) to h_res; waits
+template <class T>
+int batch_status_t(kkt_batch *b, hipStream_t s) {
+    k_batch_result<T><<<(unsigned)b->hs.size(), 256, 0, s>>>(static_cast<const BatchSys<T> *>(b->d_sys), 0, b->d_res);
+    HIPCHK(hipGetLastError());
+    return KKT_OK;
+}
+int batch_read(kkt_batch *b, hipStream_t s) {
+    HIPCHK(hipMemcpyAsync(b->h_res, b->d_res, sizeof(BatchResult) * b->hs.size(), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    return KKT_OK;
 }
 
 }  // namespace
@@ -303,8 +463,24 @@ int kkt_batch_create(kkt_handle *const *handles, int32_t count, kkt_batch **out)
     if (rc) { batch_free(b); return rc; }
     const size_t off_parts = (sysbytes.size() + 255) & ~size_t(255);
     const size_t off_vals = (off_parts + parts.size() * sizeof(BatchPart) + 255) & ~size_t(255);
-    const size_t total = off_vals + sizeof(double *) * count;
+    std::vector<int2> lord, uord;
+    try {
+        batch_order(b, true, lord);
+        batch_order(b, false, uord);
+    } catch (const std::bad_alloc &) {
+        batch_free(b);
+        return KKT_ERR_NOMEM;
+    }
+    auto after = [](size_t off, size_t bytes) { return (off + bytes + 255) & ~size_t(255); };
+    const size_t off_ptrs = after(off_vals, sizeof(double *) * count);
+    const size_t off_res = after(off_ptrs, sizeof(BatchPtrs) * count);
+    const size_t off_tick = after(off_res, sizeof(BatchResult) * count);
+    const size_t off_lord = after(off_tick, 2 * sizeof(int));
+    const size_t off_uord = after(off_lord, sizeof(int2) * lord.size());
+    const size_t total = after(off_uord, sizeof(int2) * uord.size());
     if (hipMalloc(&b->dmem, total) != hipSuccess ||
+        hipHostMalloc(reinterpret_cast<void **>(&b->h_ptrs), sizeof(BatchPtrs) * count) != hipSuccess ||
+        hipHostMalloc(reinterpret_cast<void **>(&b->h_res), sizeof(BatchResult) * count) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void **>(&b->h_vals), sizeof(double *) * count) != hipSuccess ||
         hipEventCreateWithFlags(&b->vals_done, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&b->graph_done, hipEventDisableTiming) != hipSuccess ||
@@ -336,6 +512,38 @@ int kkt_batch_create(kkt_handle *const *handles, int32_t count, kkt_batch **out)
     b->d_sys = b->dmem;
     b->d_parts = reinterpret_cast<BatchPart *>(b->dmem + off_parts);
     b->d_vals = reinterpret_cast<const double **>(b->dmem + off_vals);
+    b->d_ptrs = reinterpret_cast<BatchPtrs *>(b->dmem + off_ptrs);
+    b->d_res = reinterpret_cast<BatchResult *>(b->dmem + off_res);
+    b->d_tick = reinterpret_cast<int *>(b->dmem + off_tick);
+    b->d_lord = reinterpret_cast<int2 *>(b->dmem + off_lord);
+    b->d_uord = reinterpret_cast<int2 *>(b->dmem + off_uord);
+    b->nl = (int)lord.size();
+    b->nu = (int)uord.size();
+    for (auto *h : b->hs) {
+        b->nmax = std::max(b->nmax, h->sym.n);
+        b->nbmax = std::max(b->nbmax, norm_blocks(h->sym.n));
+    }
+    {
+        int bl = 0, bu = 0;
+        auto occ = [&](auto tag) {
+            using T = decltype(tag);
+            return hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                       &bl, reinterpret_cast<const void *>(&k_batch_solve<true, T>), kPersThreads, 0) == hipSuccess &&
+                   hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                       &bu, reinterpret_cast<const void *>(&k_batch_solve<false, T>), kPersThreads, 0) == hipSuccess;
+        };
+        if (!(b->fp32 ? occ(float{}) : occ(double{}))) {
+            batch_free(b);
+            return KKT_ERR_DEVICE;
+        }
+        b->grid_l = std::max(1, bl) * b->hs[0]->ncu;
+        b->grid_u = std::max(1, bu) * b->hs[0]->ncu;
+    }
+    if ((!lord.empty() && hipMemcpy(b->d_lord, lord.data(), sizeof(int2) * lord.size(), hipMemcpyHostToDevice) != hipSuccess) ||
+        (!uord.empty() && hipMemcpy(b->d_uord, uord.data(), sizeof(int2) * uord.size(), hipMemcpyHostToDevice) != hipSuccess)) {
+        batch_free(b);
+        return KKT_ERR_DEVICE;
+    }
     if (hipMemcpy(b->d_sys, sysbytes.data(), sysbytes.size(), hipMemcpyHostToDevice) != hipSuccess ||
         (!parts.empty() && hipMemcpy(b->d_parts, parts.data(), parts.size() * sizeof(BatchPart),
                                      hipMemcpyHostToDevice) != hipSuccess) ||
@@ -402,25 +610,72 @@ int kkt_batch_refine(kkt_batch *b, const double *const *d_b, double *const *d_x,
         if (!d_b[i] || !d_x[i]) return KKT_ERR_ARG;
     DeviceGuard dg(b->device);
     if (!dg.ok) return KKT_ERR_DEVICE;
-    // the refinement streams start after everything enqueued on the caller's stream so far
-    HIPCHK(hipEventRecord(b->ready, stream));
-    for (hipStream_t st : b->rstreams) HIPCHK(hipStreamWaitEvent(st, b->ready, 0));
     std::vector<int> rcs(count, KKT_OK);
     std::vector<kkt_info> infs(count);
-    std::atomic<int> next(0);
-    auto work = [&](hipStream_t st) {
-        (void)hipSetDevice(b->device);
-        for (int i; (i = next.fetch_add(1)) < count;)
-            rcs[i] = kkt_refine(b->hs[i], d_b[i], d_x[i], 1, b->hs[i]->sym.n, &infs[i], st);
-    };
-    std::vector<std::thread> pool;
-    try {
-        for (size_t t = 1; t < b->rstreams.size(); ++t) pool.emplace_back(work, b->rstreams[t]);
-    } catch (...) {
-        // fewer threads: the remaining handles go to the ones that started
+    // the first solves of all handles together, where every handle can take part: refactored, on
+    // the workspace of the batch, not profiled, solving in place of nothing, its factors sound
+    bool merged = true;
+    for (int i = 0; i < count; ++i) {
+        const kkt_handle *h = b->hs[i];
+        merged &= h->bound && h->factored && h->ws == b->ws[i] && !h->prof && h->opts.persistent_solve != 0;
+        for (int j = 0; j < count && merged; ++j) merged &= d_b[i] != d_x[j] && (i == j || d_x[i] != d_x[j]);
     }
-    work(b->rstreams[0]);
-    for (auto &t : pool) t.join();
+    std::vector<char> solved(count, 0);
+    if (merged) {
+        int rc = b->fp32 ? batch_status_t<float>(b, stream) : batch_status_t<double>(b, stream);
+        if (!rc) rc = batch_read(b, stream);
+        if (rc) return rc;
+        for (int i = 0; i < count; ++i)
+            merged &= !(b->h_res[i].st.flags & (kFlagInternal | kFlagNonfinite)) && !b->h_res[i].st.abort;
+    }
+    if (merged) {
+        // the staging was last read before the wait above
+        for (int i = 0; i < count; ++i) b->h_ptrs[i] = BatchPtrs{b->hs[i]->d_values, d_b[i], d_x[i]};
+        HIPCHK(hipMemcpyAsync(b->d_ptrs, b->h_ptrs, sizeof(BatchPtrs) * count, hipMemcpyHostToDevice, stream));
+        int rc = b->fp32 ? batch_first_solves_t<float>(b, stream) : batch_first_solves_t<double>(b, stream);
+        if (!rc) rc = batch_read(b, stream);
+        if (rc) return rc;
+        for (int i = 0; i < count; ++i) {
+            const DevStatus &st = b->h_res[i].st;
+            const ResNorms &rn = b->h_res[i].rn;
+            infs[i].perturbed_pivots = (int64_t)st.perturbed;
+            if (st.abort) {
+                rcs[i] = KKT_ERR_DEVICE;
+                solved[i] = 2;
+                continue;
+            }
+            const double den = st.anorm * rn.xnorm + rn.bnorm;
+            infs[i].berr = den == 0.0 ? (rn.rnorm == 0.0 ? 0.0 : INFINITY) : rn.rnorm / den;
+            solved[i] = infs[i].berr <= b->hs[i]->opts.berr_tol ? 2 : 1;   // 2: done
+        }
+    }
+    // the rest by worker threads on streams that start after everything enqueued so far
+    if (std::any_of(solved.begin(), solved.end(), [](char c) { return c != 2; })) {
+        HIPCHK(hipEventRecord(b->ready, stream));
+        for (hipStream_t st : b->rstreams) HIPCHK(hipStreamWaitEvent(st, b->ready, 0));
+        std::atomic<int> next(0);
+        auto work = [&](hipStream_t st) {
+            (void)hipSetDevice(b->device);
+            for (int i; (i = next.fetch_add(1)) < count;) {
+                if (solved[i] == 2) continue;
+                if (solved[i] == 0) {
+                    rcs[i] = kkt_refine(b->hs[i], d_b[i], d_x[i], 1, b->hs[i]->sym.n, &infs[i], st);
+                    continue;
+                }
+                const int64_t pert = infs[i].perturbed_pivots;
+                rcs[i] = fgmres_column(b->hs[i], d_b[i], d_x[i], &infs[i], st, kSolved);
+                infs[i].perturbed_pivots = pert;
+            }
+        };
+        std::vector<std::thread> pool;
+        try {
+            for (size_t t = 1; t < b->rstreams.size(); ++t) pool.emplace_back(work, b->rstreams[t]);
+        } catch (...) {
+            // fewer threads: the remaining handles go to the ones that started
+        }
+        work(b->rstreams[0]);
+        for (auto &t : pool) t.join();
+    }
     int worst = KKT_OK;
     for (int i = 0; i < count; ++i) {
         if (info) info[i] = infs[i];

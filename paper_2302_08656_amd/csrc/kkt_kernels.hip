@@ -2489,24 +2489,18 @@ __global__ __launch_bounds__(256) void k_unpermute(int n, const int32_t *__restr
 // ---------------------------------------------------------------------------------------
 // residual, sparse products and Krylov vector kernels (FP64)
 
-// res = b - A x (8 lanes per row, kRowsPerGroup rows per group, grid-stride) and block
-// maxima of |res|, |x|, |b| into part[3 * block + {0, 1, 2}]; v0, x0, b0 null: those of the
-// recorded call.  Column blockIdx.y: x and b at + ld, block maxima after the other columns'; res
-// null: maxima only
-__global__ __launch_bounds__(256) void k_residual(int n, const int32_t *__restrict__ rowptr,
-                                                  const int32_t *__restrict__ col, const double *v0,
-                                                  const double *x0, const double *b0, int64_t ld,
-                                                  const CallPtrs *call, double *__restrict__ res,
-                                                  double *__restrict__ part) {
+// res = b - A x (8 lanes per row, kRowsPerGroup rows per group, grid-stride over nblk blocks) and
+// block maxima of |res|, |x|, |b| into part[3 * blk + {0, 1, 2}]; res null: maxima only
+__device__ __forceinline__ void residual_body(int blk, int nblk, int n, const int32_t *__restrict__ rowptr,
+                                              const int32_t *__restrict__ col, const double *__restrict__ v,
+                                              const double *__restrict__ x, const double *__restrict__ b,
+                                              double *__restrict__ res, double *__restrict__ part) {
     __shared__ double red[3][4];
-    const double *__restrict__ v = v0 ? v0 : call_ptr(&call->v);
-    const double *__restrict__ x = x0 ? x0 + blockIdx.y * ld : call_x(call);
-    const double *__restrict__ b = b0 ? b0 + blockIdx.y * ld : call_ptr(&call->b);
     const double qnan = __longlong_as_double(0x7ff8000000000000LL);
     double rn = 0.0, xn = 0.0, bn = 0.0;
     const int gl = threadIdx.x & 7;
-    for (int i0 = ((blockIdx.x * blockDim.x + threadIdx.x) >> 3) * kRowsPerGroup; i0 < n;
-         i0 += ((gridDim.x * blockDim.x) >> 3) * kRowsPerGroup) {
+    for (int i0 = ((blk * blockDim.x + threadIdx.x) >> 3) * kRowsPerGroup; i0 < n;
+         i0 += ((nblk * blockDim.x) >> 3) * kRowsPerGroup) {
         int rp[kRowsPerGroup + 1];
         group_rows(rowptr, n, i0, rp);
         double vv[kRowsPerGroup], xv[kRowsPerGroup];
@@ -2553,8 +2547,20 @@ __global__ __launch_bounds__(256) void k_residual(int n, const int32_t *__restri
             const double y = red[threadIdx.x][q];
             t = (isnan(t) || isnan(y)) ? t + y : fmax(t, y);
         }
-        part[3 * (blockIdx.y * gridDim.x + blockIdx.x) + threadIdx.x] = t;
+        part[3 * blk + threadIdx.x] = t;
     }
+}
+
+// v0, x0, b0 null: those of the recorded call.  Column blockIdx.y: x and b at + ld, block maxima
+// after the other columns'
+__global__ __launch_bounds__(256) void k_residual(int n, const int32_t *__restrict__ rowptr,
+                                                  const int32_t *__restrict__ col, const double *v0,
+                                                  const double *x0, const double *b0, int64_t ld,
+                                                  const CallPtrs *call, double *__restrict__ res,
+                                                  double *__restrict__ part) {
+    residual_body(blockIdx.x, gridDim.x, n, rowptr, col, v0 ? v0 : call_ptr(&call->v),
+                  x0 ? x0 + blockIdx.y * ld : call_x(call), b0 ? b0 + blockIdx.y * ld : call_ptr(&call->b), res,
+                  part + 3 * (int64_t)blockIdx.y * gridDim.x);
 }
 
 __global__ void k_spmv(int n, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
