@@ -18,7 +18,7 @@ struct BatchSys {
     RefArgs<T> ref;
     const int32_t *a_rowptr, *a_colind, *colptr, *Q;
     const int2 *lu_src;
-    double *r, *c, *part;
+    double *r, *c;
     int16_t *er, *ec;
     int n, eq, nb_norm;
     CopyRanges rest;   // the copy after the last level
@@ -88,13 +88,7 @@ __global__ __launch_bounds__(256) void k_batch_rowsums(const BatchSys<T> *__rest
                                                        const double *const *__restrict__ vals) {
     const BatchPart P = parts[find_part(parts, nparts, blockIdx.x)];
     const BatchSys<T> &S = sys[P.sys];
-    norms_body(blockIdx.x - P.blk0, P.nblk, S.n, S.a_rowptr, S.a_colind, vals[P.sys], S.r, S.ec, S.part);
-}
-
-template <class T>
-__global__ __launch_bounds__(256) void k_batch_norms(const BatchSys<T> *__restrict__ sys) {
-    const BatchSys<T> &S = sys[blockIdx.x];
-    max_parts_body(S.nb_norm, 2, S.part, &S.ref.st->anorm_scaled);
+    norms_body(blockIdx.x - P.blk0, S.n, S.a_rowptr, S.a_colind, vals[P.sys], S.r, S.ec, S.ref.st);
 }
 
 template <class C>
@@ -170,7 +164,7 @@ __global__ __launch_bounds__(256) void k_batch_residual(const BatchSys<T> *__res
     const BatchSys<T> &S = sys[blockIdx.y];
     if ((int)blockIdx.x >= S.nb_norm) return;
     const BatchPtrs p = ptrs[blockIdx.y];
-    residual_body(blockIdx.x, S.nb_norm, S.n, S.a_rowptr, S.a_colind, p.v, p.x, p.b, nullptr, S.rpart);
+    residual_body(blockIdx.x, S.nb_norm, S.n, S.a_rowptr, S.a_colind, p.v, p.x, p.b, nullptr, S.rpart, nullptr);
 }
 
 template <class T>
@@ -210,7 +204,7 @@ struct kkt_batch {
     const double **d_vals = nullptr;
     const double **h_vals = nullptr;   // pinned staging of the value pointers
     hipEvent_t vals_done = nullptr;    // the last upload of h_vals has been read
-    // launches of a step: kind (0 clear, 1 rows, 2 cols, 3 scatter, 4 norms, 5 level,
+    // launches of a step: kind (0 clear, 1 rows, 2 cols, 3 norms, 5 level,
     // 6 copy, 7 counts, 8 wavefront level, 9 the same with many narrow items), grid, first share,
     // shares
     struct Launch {
@@ -254,7 +248,6 @@ BatchSys<T> batch_sys(const kkt_handle *h) {
     b.c = d.c;
     b.er = d.er;
     b.ec = d.ec;
-    b.part = d.part;
     b.n = h->sym.n;
     b.eq = h->opts.equilibrate != 0;
     b.nb_norm = norm_blocks(h->sym.n);
@@ -281,8 +274,8 @@ int batch_build(kkt_batch *b, std::vector<BatchPart> &parts, std::vector<char> &
     auto add = [&](int kind, const std::vector<BatchPart> &ps) {
         int grid = 0;
         for (const auto &p : ps) grid = std::max(grid, p.blk0 + p.nblk);
-        if (grid == 0 && kind != 0 && kind != 4 && kind != 7) return;
-        b->launches.push_back({kind, kind == 0 || kind == 4 || kind == 7 ? count : grid, (int)parts.size(),
+        if (grid == 0 && kind != 0 && kind != 7) return;
+        b->launches.push_back({kind, kind == 0 || kind == 7 ? count : grid, (int)parts.size(),
                                (int)ps.size()});
         parts.insert(parts.end(), ps.begin(), ps.end());
     };
@@ -304,8 +297,7 @@ int batch_build(kkt_batch *b, std::vector<BatchPart> &parts, std::vector<char> &
     add(0, {});
     add(1, shares([&](int i, BatchPart &) { return row_blocks(sys[i].n); }));
     add(2, shares([&](int i, BatchPart &) { return col_blocks(sys[i].n); }));
-    add(3, shares([&](int i, BatchPart &) { return sys[i].nb_norm; }));
-    add(4, {});
+    add(3, shares([&](int i, BatchPart &) { return sum_blocks(sys[i].n); }));
     int nlev = 0;
     for (auto *h : b->hs) nlev = std::max(nlev, (int)h->sch.f_lvl.size() - 1);
     for (int l = 0; l < nlev; ++l) {
@@ -351,7 +343,6 @@ int batch_enqueue(kkt_batch *b, hipStream_t s) {
             case 1: k_batch_rows<T><<<L.grid, 256, 0, s>>>(sys, p, L.np, b->d_vals); break;
             case 2: k_batch_cols<T><<<L.grid, 256, 0, s>>>(sys, p, L.np, b->d_vals); break;
             case 3: k_batch_rowsums<T><<<L.grid, 256, 0, s>>>(sys, p, L.np, b->d_vals); break;
-            case 4: k_batch_norms<T><<<L.grid, 256, 0, s>>>(sys); break;
             case 5: k_batch_level<Big><<<L.grid, Big::kThreads, Big::kLds, s>>>(sys, p, L.np); break;
             case 6: k_batch_copy<T><<<L.grid, 256, 0, s>>>(sys, p, L.np); break;
             case 7: k_batch_counts<T><<<L.grid, 256, 0, s>>>(sys); break;

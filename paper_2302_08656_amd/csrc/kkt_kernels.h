@@ -25,4 +25,10 @@ struct ResNorms {
     double rnorm, xnorm, bnorm;
 };
 
+// What one recorded step reports to the host.
+struct StepReport {
+    DevStatus st;
+    ResNorms rn;
+};
+
 }  // namespace kkt

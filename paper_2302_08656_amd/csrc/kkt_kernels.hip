@@ -46,9 +46,12 @@ __device__ __forceinline__ double scale_of(int e) { return ldexp(1.0, -e); }
 __device__ __forceinline__ double inv_pow2_floor_log2(double m) { return scale_of(pow2_floor_log2(m)); }
 
 
-// max of non-negative doubles through their ordered bit patterns
+// max of non-negative doubles (or NaN, which stays) through their ordered bit patterns; most
+// callers find a larger value there and leave it
 __device__ __forceinline__ void atomic_max_pos(double *addr, double v) {
-    atomicMax(reinterpret_cast<unsigned long long *>(addr), (unsigned long long)__double_as_longlong(v));
+    unsigned long long *p = reinterpret_cast<unsigned long long *>(addr);
+    const unsigned long long b = (unsigned long long)__double_as_longlong(fabs(v));
+    if (b > __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(p, b);
 }
 
 // Cross-lane moves on the vector ALU (DPP and the permlane swaps): a few cycles each, where a
@@ -188,9 +191,10 @@ struct CallPtrs {
 // stores the call's inputs and clears the status words and pivot counters of the call
 // (one block of 256 threads)
 __global__ __launch_bounds__(256) void k_set_call(CallPtrs *dst, const double *v, const double *b, double *x,
-                                                  DevStatus *st, unsigned long long *pcount) {
+                                                  DevStatus *st, unsigned long long *pcount, ResNorms *rn) {
     clear_status_body(st, pcount);
     if (threadIdx.x == 0) {
+        *rn = ResNorms{0.0, 0.0, 0.0};   // maxima of the step's residual
         dst->v = v;
         dst->b = b;
         dst->x = x;
@@ -279,10 +283,36 @@ __global__ __launch_bounds__(256) void k_row_scale(int n, const int32_t *__restr
 // c[Q[j]] = 2^-floor(log2 max_i |r_i a_i,Q[j]|); then lu[p] = (r_i a) c (exact in FP64;
 // rounded once when the factor is FP32), 0 for fill-in.  The factor is written in its own
 // order (no scattered stores); the first kColRegs slots of each lane keep r_i a in registers
-// between the two sweeps, later slots of a long column are gathered again.  kColLanes lanes
-// per column, so that each lane has several gathers in flight.
+// between the two sweeps, later slots of a long column are gathered again, kColBatch at once:
+// the launch is as long as its longest column (hundreds of slots near the root of the
+// elimination tree), which takes two dependent loads a batch and sweep.  kColLanes lanes per
+// column, so that each lane has several gathers in flight.  19,000 columns: 11.9 us, 665,000:
+// 122 us (one slot of a long column at a time: 22 and 152 us); 4 lanes a column, or batches of 4:
+// 10-35 and 10 us more at 665,000.
 constexpr int kColLanes = 8;
 constexpr int kColRegs = 4;
+constexpr int kColBatch = 16;
+
+// r_i a of the kColBatch slots p, p + kColLanes, ... < p1 of a column: -1 for a slot of fill-in
+// (and its value 0); loads past the end or without an entry read the first slot's or value's
+__device__ __forceinline__ void col_batch(int p, int p1, const int2 *__restrict__ src, const double *__restrict__ v,
+                                          const int16_t *__restrict__ er, double (&ra)[kColBatch]) {
+    int2 f[kColBatch];
+    int e[kColBatch];
+#pragma unroll
+    for (int k = 0; k < kColBatch; ++k) {
+        const int q = p + kColLanes * k;
+        f[k] = src[q < p1 ? q : p];
+        if (q >= p1) f[k].x = -1;
+    }
+#pragma unroll
+    for (int k = 0; k < kColBatch; ++k) {
+        ra[k] = v[max(f[k].x, 0)];
+        e[k] = er[f[k].x >= 0 ? f[k].y : 0];
+    }
+#pragma unroll
+    for (int k = 0; k < kColBatch; ++k) ra[k] = f[k].x >= 0 ? scale_of(e[k]) * ra[k] : 0.0;
+}
 
 template <class T>
 __device__ __forceinline__ void col_store_body(int blk, int n, const int32_t *__restrict__ colptr,
@@ -305,9 +335,11 @@ __device__ __forceinline__ void col_store_body(int blk, int n, const int32_t *__
     double m = 0.0;
 #pragma unroll
     for (int k = 0; k < kColRegs; ++k) m = fmax(m, fabs(ra[k]));
-    for (int p = p0 + gl + kColLanes * kColRegs; p < p1; p += kColLanes) {
-        const int2 f = src[p];
-        if (f.x >= 0) m = fmax(m, fabs(scale_of(er[f.y]) * v[f.x]));
+    for (int p = p0 + gl + kColLanes * kColRegs; p < p1; p += kColLanes * kColBatch) {
+        double rb[kColBatch];
+        col_batch(p, p1, src, v, er, rb);
+#pragma unroll
+        for (int k = 0; k < kColBatch; ++k) m = fmax(m, fabs(rb[k]));
     }
     for (int o = kColLanes / 2; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, kColLanes));
     const int ej = scale ? pow2_floor_log2(m) : 0;
@@ -321,9 +353,12 @@ __device__ __forceinline__ void col_store_body(int blk, int n, const int32_t *__
         const int p = p0 + gl + kColLanes * k;
         if (p < p1) lu[p] = e[k].x >= 0 ? (T)(ra[k] * cj) : T(0);
     }
-    for (int p = p0 + gl + kColLanes * kColRegs; p < p1; p += kColLanes) {
-        const int2 f = src[p];
-        lu[p] = f.x >= 0 ? (T)((scale_of(er[f.y]) * v[f.x]) * cj) : T(0);
+    for (int p = p0 + gl + kColLanes * kColRegs; p < p1; p += kColLanes * kColBatch) {
+        double rb[kColBatch];
+        col_batch(p, p1, src, v, er, rb);
+#pragma unroll
+        for (int k = 0; k < kColBatch; ++k)
+            if (p + kColLanes * k < p1) lu[p + kColLanes * k] = (T)(rb[k] * cj);
     }
 }
 
@@ -336,77 +371,40 @@ __global__ __launch_bounds__(256) void k_col_store(int n, const int32_t *__restr
     col_store_body<T>(blockIdx.x, n, colptr, src, Q, call_ptr(&call->v), er, scale, c, ec, lu);
 }
 
-// The row sums of |A| and |R A C| in CSR order, kRowsPerGroup rows per group of 8 lanes
-// (grid-stride): the lanes load 8 consecutive entries of each row at once and leave their
-// terms in LDS, and lane k of the group adds row k's terms in CSR order (so the sums are
-// the sequential ones, bit for bit); block maxima into part[2 * block].  blockDim.x <= 256.
-__device__ __forceinline__ void norms_body(int blk, int nblk, int n, const int32_t *__restrict__ rowptr,
+// The largest row sums of |R A C| and |A| into st (cleared before), one row per lane: its terms
+// are added in CSR order (so the sums are the sequential ones, bit for bit), kNormBatch loaded at
+// once.  Bound by the chain row pointer, column, its scale, and on large systems by the gathers:
+// most rows have one batch, so a lane has its whole row in flight.  19,000 rows: 8.4 us, 665,000
+// rows: 40 us (rows spread over 8 lanes, their terms exchanged through LDS, and a further launch
+// to reduce the blocks' maxima: 20.4 and 51 us).
+constexpr int kNormBatch = 8;
+__device__ __forceinline__ void norms_body(int blk, int n, const int32_t *__restrict__ rowptr,
                                            const int32_t *__restrict__ col, const double *__restrict__ v,
                                            const double *__restrict__ r, const int16_t *__restrict__ ec,
-                                           double *__restrict__ part) {
+                                           DevStatus *st) {
     __shared__ double red[2][4];
-    __shared__ double terms[256 / 8][kRowsPerGroup][2][8];   // per group: row, {|r a c|, |a|}, entry
-    const int gl = threadIdx.x & 7, grp = threadIdx.x >> 3;
-    double (*T)[2][8] = terms[grp];
+    const int i = blk * blockDim.x + threadIdx.x;
     double s = 0.0, a = 0.0;
-    for (int i0 = ((blk * blockDim.x + threadIdx.x) >> 3) * kRowsPerGroup; i0 < n;
-         i0 += ((nblk * blockDim.x) >> 3) * kRowsPerGroup) {
-        int rp[kRowsPerGroup + 1];
-        group_rows(rowptr, n, i0, rp);
-        double ri[kRowsPerGroup], vv[kRowsPerGroup], cj[kRowsPerGroup];
-        int cc[kRowsPerGroup];
+    if (i < n) {
+        const int p1 = rowptr[i + 1];
+        const double ri = r[i];
+        for (int p = rowptr[i]; p < p1; p += kNormBatch) {
+            double x[kNormBatch];
+            int c[kNormBatch];
 #pragma unroll
-        for (int k = 0; k < kRowsPerGroup; ++k) {
-            const int p = rp[k] + gl;
-            const bool h = p < rp[k + 1];
-            ri[k] = i0 + k < n ? r[i0 + k] : 0.0;
-            vv[k] = h ? v[p] : 0.0;
-            cc[k] = h ? col[p] : 0;
-        }
-#pragma unroll
-        for (int k = 0; k < kRowsPerGroup; ++k) cj[k] = rp[k] + gl < rp[k + 1] ? scale_of(ec[cc[k]]) : 0.0;
-#pragma unroll
-        for (int k = 0; k < kRowsPerGroup; ++k) {
-            T[k][0][gl] = fabs((ri[k] * vv[k]) * cj[k]);
-            T[k][1][gl] = fabs(vv[k]);
-        }
-        __builtin_amdgcn_wave_barrier();
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        // lane k: row k's first (up to) 8 terms in order
-        const int k = gl < kRowsPerGroup ? gl : 0;
-        const int len0 = min(8, rp[k + 1] - rp[k]);
-        double si = 0.0, ai = 0.0;
-        if (gl < kRowsPerGroup)
-            for (int t = 0; t < len0; ++t) {
-                si = si + T[k][0][t];
-                ai = ai + T[k][1][t];
+            for (int k = 0; k < kNormBatch; ++k) {
+                const int q = p + k < p1 ? p + k : p;
+                x[k] = v[q];
+                c[k] = col[q];
             }
-        // longer rows: the group loads each further chunk of 8, the row's lane adds it
 #pragma unroll
-        for (int kk = 0; kk < kRowsPerGroup; ++kk) {
-            for (int q = rp[kk] + 8; q < rp[kk + 1]; q += 8) {
-                __builtin_amdgcn_wave_barrier();
-                __atomic_signal_fence(__ATOMIC_SEQ_CST);
-                const bool h = q + gl < rp[kk + 1];
-                const double x = h ? v[q + gl] : 0.0;
-                T[0][0][gl] = h ? fabs((ri[kk] * x) * scale_of(ec[col[q + gl]])) : 0.0;
-                T[0][1][gl] = fabs(x);
-                __builtin_amdgcn_wave_barrier();
-                __atomic_signal_fence(__ATOMIC_SEQ_CST);
-                if (gl == kk) {
-                    const int cnt = min(8, rp[kk + 1] - q);
-                    for (int t = 0; t < cnt; ++t) {
-                        si = si + T[0][0][t];
-                        ai = ai + T[0][1][t];
-                    }
-                }
+            for (int k = 0; k < kNormBatch; ++k) c[k] = ec[c[k]];
+#pragma unroll
+            for (int k = 0; k < kNormBatch; ++k) {
+                const double xs = p + k < p1 ? x[k] : 0.0;   // adds an exact zero past the row's end
+                s = s + fabs((ri * xs) * scale_of(c[k]));
+                a = a + fabs(xs);
             }
-        }
-        __builtin_amdgcn_wave_barrier();
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        if (gl < kRowsPerGroup) {
-            s = fmax(s, si);
-            a = fmax(a, ai);
         }
     }
     for (int o = 32; o > 0; o >>= 1) {
@@ -419,16 +417,16 @@ __device__ __forceinline__ void norms_body(int blk, int nblk, int n, const int32
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        part[2 * blk] = fmax(fmax(red[0][0], red[0][1]), fmax(red[0][2], red[0][3]));
-        part[2 * blk + 1] = fmax(fmax(red[1][0], red[1][1]), fmax(red[1][2], red[1][3]));
+        atomic_max_pos(&st->anorm_scaled, fmax(fmax(red[0][0], red[0][1]), fmax(red[0][2], red[0][3])));
+        atomic_max_pos(&st->anorm, fmax(fmax(red[1][0], red[1][1]), fmax(red[1][2], red[1][3])));
     }
 }
 
 __global__ __launch_bounds__(256) void k_norms(int n, const int32_t *__restrict__ rowptr,
                                                const int32_t *__restrict__ col, const CallPtrs *call,
                                                const double *__restrict__ r, const int16_t *__restrict__ ec,
-                                               double *__restrict__ part) {
-    norms_body(blockIdx.x, gridDim.x, n, rowptr, col, call_ptr(&call->v), r, ec, part);
+                                               DevStatus *st) {
+    norms_body(blockIdx.x, n, rowptr, col, call_ptr(&call->v), r, ec, st);
 }
 
 // max that propagates a NaN of either side
@@ -2490,11 +2488,15 @@ __global__ __launch_bounds__(256) void k_unpermute(int n, const int32_t *__restr
 // residual, sparse products and Krylov vector kernels (FP64)
 
 // res = b - A x (8 lanes per row, kRowsPerGroup rows per group, grid-stride over nblk blocks) and
-// block maxima of |res|, |x|, |b| into part[3 * blk + {0, 1, 2}]; res null: maxima only
+// block maxima of |res|, |x|, |b| into part[3 * blk + {0, 1, 2}], or with acc the maxima into acc
+// (cleared before); res null: maxima only.  Bound by the chain row pointer, column, x: two entries
+// of every row a lane, and the right-hand sides, are in flight together (19,000 rows: 9.2 us, with
+// a launch for the maxima and the later loads one by one 16.7 us; 665,000 rows: 45.5 and 48.8 us).
 __device__ __forceinline__ void residual_body(int blk, int nblk, int n, const int32_t *__restrict__ rowptr,
                                               const int32_t *__restrict__ col, const double *__restrict__ v,
                                               const double *__restrict__ x, const double *__restrict__ b,
-                                              double *__restrict__ res, double *__restrict__ part) {
+                                              double *__restrict__ res, double *__restrict__ part,
+                                              ResNorms *acc) {
     __shared__ double red[3][4];
     const double qnan = __longlong_as_double(0x7ff8000000000000LL);
     double rn = 0.0, xn = 0.0, bn = 0.0;
@@ -2503,30 +2505,36 @@ __device__ __forceinline__ void residual_body(int blk, int nblk, int n, const in
          i0 += ((nblk * blockDim.x) >> 3) * kRowsPerGroup) {
         int rp[kRowsPerGroup + 1];
         group_rows(rowptr, n, i0, rp);
-        double vv[kRowsPerGroup], xv[kRowsPerGroup];
-        int cc[kRowsPerGroup];
+        // two entries of every row a lane at once (past a row's end the first entry's, not used),
+        // and lane k's right-hand side and unknown of row k
+        double vv[kRowsPerGroup][2], xv[kRowsPerGroup][2];
 #pragma unroll
-        for (int k = 0; k < kRowsPerGroup; ++k) {
-            const int p = rp[k] + gl;
-            const bool h = p < rp[k + 1];
-            vv[k] = h ? v[p] : 0.0;
-            cc[k] = h ? col[p] : 0;
-        }
+        for (int k = 0; k < kRowsPerGroup; ++k)
 #pragma unroll
-        for (int k = 0; k < kRowsPerGroup; ++k) xv[k] = rp[k] + gl < rp[k + 1] ? x[cc[k]] : 0.0;
-#pragma unroll
-        for (int k = 0; k < kRowsPerGroup; ++k) {
-            double sk = vv[k] * xv[k];
-            for (int p = rp[k] + gl + 8; p < rp[k + 1]; p += 8) sk = fma(v[p], x[col[p]], sk);
-            sk = group_sum(sk, 8);
-            const int i = i0 + k;
-            if (gl == 0 && i < n) {
-                const double ri = b[i] - sk;
-                if (res) res[i] = ri;
-                rn = isnan(ri) ? qnan : fmax(rn, fabs(ri));
-                xn = isnan(x[i]) ? qnan : fmax(xn, fabs(x[i]));
-                bn = fmax(bn, fabs(b[i]));
+            for (int t = 0; t < 2; ++t) {
+                const int p = rp[k] + gl + 8 * t, q = p < rp[k + 1] ? p : 0;
+                vv[k][t] = v[q];
+                xv[k][t] = x[col[q]];
             }
+        const int i = i0 + gl;
+        const bool own = gl < kRowsPerGroup && i < n;
+        const double bi = b[own ? i : 0], xi = x[own ? i : 0];
+        double mine = 0.0;
+#pragma unroll
+        for (int k = 0; k < kRowsPerGroup; ++k) {
+            int p = rp[k] + gl;
+            double sk = p < rp[k + 1] ? vv[k][0] * xv[k][0] : 0.0;
+            if (p + 8 < rp[k + 1]) sk = fma(vv[k][1], xv[k][1], sk);
+            for (p += 16; p < rp[k + 1]; p += 8) sk = fma(v[p], x[col[p]], sk);
+            sk = group_sum(sk, 8);
+            if (gl == k) mine = sk;
+        }
+        if (own) {
+            const double ri = bi - mine;
+            if (res) res[i] = ri;
+            rn = isnan(ri) ? qnan : fmax(rn, fabs(ri));
+            xn = isnan(xi) ? qnan : fmax(xn, fabs(xi));
+            bn = fmax(bn, fabs(bi));
         }
     }
     for (int o = 32; o > 0; o >>= 1) {
@@ -2547,7 +2555,8 @@ __device__ __forceinline__ void residual_body(int blk, int nblk, int n, const in
             const double y = red[threadIdx.x][q];
             t = (isnan(t) || isnan(y)) ? t + y : fmax(t, y);
         }
-        part[3 * blk + threadIdx.x] = t;
+        if (acc) atomic_max_pos(threadIdx.x == 0 ? &acc->rnorm : threadIdx.x == 1 ? &acc->xnorm : &acc->bnorm, t);
+        else part[3 * blk + threadIdx.x] = t;
     }
 }
 
@@ -2557,10 +2566,18 @@ __global__ __launch_bounds__(256) void k_residual(int n, const int32_t *__restri
                                                   const int32_t *__restrict__ col, const double *v0,
                                                   const double *x0, const double *b0, int64_t ld,
                                                   const CallPtrs *call, double *__restrict__ res,
-                                                  double *__restrict__ part) {
+                                                  double *__restrict__ part, ResNorms *acc) {
     residual_body(blockIdx.x, gridDim.x, n, rowptr, col, v0 ? v0 : call_ptr(&call->v),
                   x0 ? x0 + blockIdx.y * ld : call_x(call), b0 ? b0 + blockIdx.y * ld : call_ptr(&call->b), res,
-                  part + 3 * (int64_t)blockIdx.y * gridDim.x);
+                  part + 3 * (int64_t)blockIdx.y * gridDim.x, acc);
+}
+
+// a step's status and residual norms to pinned host memory, its last launch
+__global__ void k_report(const DevStatus *st, const ResNorms *rn, StepReport *out) {
+    if (threadIdx.x == 0) {
+        out->st = *st;
+        out->rn = *rn;
+    }
 }
 
 __global__ void k_spmv(int n, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,

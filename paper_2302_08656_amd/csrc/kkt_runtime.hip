@@ -206,6 +206,7 @@ inline int row_blocks(int n) {
     return (int)std::max<unsigned>(1, blocks_for((int64_t)(n + kRowsPerGroup - 1) / kRowsPerGroup * 8, 256));
 }
 inline int col_blocks(int n) { return (int)std::max<unsigned>(1, blocks_for((int64_t)n * kColLanes, 256)); }
+inline int sum_blocks(int n) { return (int)std::max<unsigned>(1, blocks_for(n, 256)); }   // one row per lane
 inline int norm_blocks(int n) { return std::min(kNormRowBlocks, row_blocks(n)); }
 // blocks of `threads` threads for ns narrow items, the last nt of them tiny (one 16-lane
 // group per item, one kTinyLanes-lane group per tiny item)
@@ -384,7 +385,7 @@ int enqueue_solve_cols(kkt_handle *h, const double *b, double *x, int ncol, int6
 // stores the call's values (and right-hand side and solution, or null) for the recorded
 // kernels and clears the status words (before anything of the call can raise a flag)
 int set_call(kkt_handle *h, const double *v, const double *b, double *x, hipStream_t s) {
-    timed(h, KKT_PROF_UPDATE, s, [&] { k_set_call<<<1, 256, 0, s>>>(h->d.call, v, b, x, h->d.st, h->d.pcount); });
+    timed(h, KKT_PROF_UPDATE, s, [&] { k_set_call<<<1, 256, 0, s>>>(h->d.call, v, b, x, h->d.st, h->d.pcount, h->d.rn); });
     HIPCHK(hipGetLastError());
     return KKT_OK;
 }
@@ -414,9 +415,9 @@ int enqueue_update(kkt_handle *h, hipStream_t s, bool setup = false, int ntick =
             return 0;
         });
     });
-    const int nbn = norm_blocks(n);
-    timed(h, KKT_PROF_UPDATE, s, [&] { k_norms<<<nbn, 256, 0, s>>>(n, d.a_rowptr, d.a_colind, d.call, d.r, d.ec, d.part); });
-    timed(h, KKT_PROF_UPDATE, s, [&] { k_max_parts<<<1, 256, 0, s>>>(nbn, 2, d.part, &d.st->anorm_scaled); });
+    timed(h, KKT_PROF_UPDATE, s, [&] {
+        k_norms<<<sum_blocks(n), 256, 0, s>>>(n, d.a_rowptr, d.a_colind, d.call, d.r, d.ec, d.st);
+    });
     HIPCHK(hipGetLastError());
     return KKT_OK;
 }
@@ -602,7 +603,7 @@ int enqueue_residual(kkt_handle *h, const double *v, const double *x, const doub
     const Dev &d = h->d;
     const int n = h->sym.n, nb = norm_blocks(n);
     timed(h, KKT_PROF_RESIDUAL, s, [&] {
-        k_residual<<<nb, 256, 0, s>>>(n, d.a_rowptr, d.a_colind, v, x, b, 0, d.call, d.res, d.part);
+        k_residual<<<nb, 256, 0, s>>>(n, d.a_rowptr, d.a_colind, v, x, b, 0, d.call, d.res, d.part, nullptr);
     });
     timed(h, KKT_PROF_RESIDUAL, s, [&] { k_max_parts<<<1, 256, 0, s>>>(nb, 3, d.part, &d.rn->rnorm); });
     HIPCHK(hipGetLastError());
@@ -614,7 +615,8 @@ int enqueue_residual_cols(kkt_handle *h, const double *x, const double *b, int n
     const Dev &d = h->d;
     const int n = h->sym.n, nb = norm_blocks(n);
     timed(h, KKT_PROF_RESIDUAL, s, [&] {
-        k_residual<<<dim3(nb, ncol), 256, 0, s>>>(n, d.a_rowptr, d.a_colind, h->d_values, x, b, ld, d.call, nullptr, d.Z);
+        k_residual<<<dim3(nb, ncol), 256, 0, s>>>(n, d.a_rowptr, d.a_colind, h->d_values, x, b, ld, d.call, nullptr, d.Z,
+                                                       nullptr);
     });
     timed(h, KKT_PROF_RESIDUAL, s, [&] { k_max_parts<<<ncol, 256, 0, s>>>(nb, 3, d.Z, &d.rn->rnorm); });
     HIPCHK(hipGetLastError());
@@ -623,12 +625,16 @@ int enqueue_residual_cols(kkt_handle *h, const double *x, const double *b, int n
 
 // berr and its denominator of ncol columns on the host from the norms of enqueue_residual
 // (_cols), and the status block read with them in *sto
-int residual_berr(kkt_handle *h, double *berr, double *den, hipStream_t s, DevStatus *sto = nullptr, int ncol = 1) {
+int residual_berr(kkt_handle *h, double *berr, double *den, hipStream_t s, DevStatus *sto = nullptr, int ncol = 1,
+                  bool reported = false) {
     const Dev &d = h->d;
     // the residual norms are carved right after the status block: one read-back takes both
     const size_t off = static_cast<size_t>(reinterpret_cast<const char *>(d.rn) - reinterpret_cast<const char *>(d.st));
     if (off < sizeof(DevStatus) || off + kMaxCols * sizeof(ResNorms) > sizeof(h->h_stage)) return KKT_ERR_DEVICE;
-    HIPCHK(hipMemcpyAsync(h->h_small, d.st, off + ncol * sizeof(ResNorms), hipMemcpyDeviceToHost, s));
+    // reported: the step's last launch wrote both to the pinned buffer
+    const size_t at = reported ? offsetof(StepReport, rn) : off;
+    if (!reported)
+        HIPCHK(hipMemcpyAsync(h->h_small, d.st, off + ncol * sizeof(ResNorms), hipMemcpyDeviceToHost, s));
     HIPCHK(sync_fold(h, s));
     DevStatus st;
     std::memcpy(&st, h->h_small, sizeof(st));
@@ -636,7 +642,7 @@ int residual_berr(kkt_handle *h, double *berr, double *den, hipStream_t s, DevSt
     if (st.abort) return KKT_ERR_DEVICE;
     for (int c = 0; c < ncol; ++c) {
         ResNorms rn;
-        std::memcpy(&rn, reinterpret_cast<const char *>(h->h_small) + off + c * sizeof(rn), sizeof(rn));
+        std::memcpy(&rn, reinterpret_cast<const char *>(h->h_small) + at + c * sizeof(rn), sizeof(rn));
         den[c] = st.anorm * rn.xnorm + rn.bnorm;
         if (den[c] == 0.0) berr[c] = rn.rnorm == 0.0 ? 0.0 : INFINITY;
         else berr[c] = rn.rnorm / den[c];
@@ -650,8 +656,20 @@ int residual_berr(kkt_handle *h, double *berr, double *den, hipStream_t s, DevSt
 int enqueue_step(kkt_handle *h, hipStream_t s) {
     int rc = enqueue_levels(h, s, true);
     if (!rc) rc = enqueue_solve(h, nullptr, nullptr, s, false);
-    if (!rc) rc = enqueue_residual(h, nullptr, nullptr, nullptr, s);
-    return rc;
+    if (rc) return rc;
+    const Dev &d = h->d;
+    const int n = h->sym.n;
+    timed(h, KKT_PROF_RESIDUAL, s, [&] {
+        k_residual<<<norm_blocks(n), 256, 0, s>>>(n, d.a_rowptr, d.a_colind, nullptr, nullptr, nullptr, 0, d.call, d.res,
+                                                  nullptr, d.rn);
+    });
+    // into the pinned buffer; a handle without one reads the status back by a copy
+    if (h->h_pinned)
+        timed(h, KKT_PROF_RESIDUAL, s, [&] {
+            k_report<<<1, 64, 0, s>>>(d.st, d.rn, reinterpret_cast<StepReport *>(h->h_pinned));
+        });
+    HIPCHK(hipGetLastError());
+    return KKT_OK;
 }
 
 // Approximate preconditioner application: `sweeps` sweeps per triangle, each triangle from
@@ -720,7 +738,7 @@ int fgmres_column(kkt_handle *h, const double *b, double *x, kkt_info *info, hip
     for (bool first = true;; first = false) {
         DevStatus st{};
         rc = fused && first ? KKT_OK : enqueue_residual(h, h->d_values, x, b, s);
-        if (!rc) rc = residual_berr(h, &berr, &den, s, &st);
+        if (!rc) rc = residual_berr(h, &berr, &den, s, &st, 1, fused && first && h->h_pinned);
         if (fused && first) {
             pert = (int64_t)st.perturbed;
             const int fst = ((st.flags & kFlagInternal) || st.abort) ? KKT_ERR_DEVICE
@@ -1147,8 +1165,8 @@ int run_step(kkt_handle *h, hipStream_t s) {
         if (cs == hipStreamCaptureStatusNone) {
             if (!h->fused) record_fused(h);
             if (h->fused) {
+                // the call waits for the replay, so no event marks its end
                 HIPCHK(hipGraphLaunch(h->fused, s));
-                HIPCHK(hipEventRecord(h->levels_done, s));
                 return KKT_OK;
             }
         }
@@ -1208,6 +1226,7 @@ int kkt_refactor_refine(kkt_handle *h, const double *d_values, const double *d_b
     h->factored = true;
     kkt_info inf{};
     rc = fgmres_column(h, b, d_x, &inf, stream, kStep);
+    if (rc == KKT_ERR_DEVICE) (void)hipStreamSynchronize(stream);   // the replay has ended on every return
     if (info && (rc >= 0 || inf.status < 0)) *info = inf;   // a failed factorization fills inf
     return rc;
 }
