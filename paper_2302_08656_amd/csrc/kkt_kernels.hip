@@ -1856,7 +1856,10 @@ __device__ __noinline__ double wait_slow(const double *p, int *abort) {
 }
 
 // re-reads every still-unset entry of a batch together until none is left (bounded; on
-// timeout or abort the unset entries read as 0 and *abort is raised)
+// timeout or abort the unset entries read as 0 and *abort is raised).  A poll takes about 1 us to
+// return, and a chain of levels waits for one poll and a half a level, so no pause is put between
+// them (1,000 buses, one solve: 124 us; with a pause of 128 clocks 127; 25,000 buses, two
+// columns: 389 and 398 us).
 template <int B>
 __device__ __forceinline__ void wait_batch(unsigned long long (&bb)[B], const double *v, const int (&cc)[B],
                                            int *abort) {
@@ -1864,7 +1867,6 @@ __device__ __forceinline__ void wait_batch(unsigned long long (&bb)[B], const do
 #pragma unroll
     for (int k = 0; k < B; ++k) pend |= bb[k] == kUnset;
     for (int it = 1; pend; ++it) {
-        __builtin_amdgcn_s_sleep(2);
 #pragma unroll
         for (int k = 0; k < B; ++k)
             if (bb[k] == kUnset) bb[k] = load_coherent(v + cc[k]);
