@@ -38,8 +38,8 @@ def parse():
                     help="factor storage and refactorization precision (refinement stays FP64); default "
                          "fp64 for the grid workloads, fp32 for the batched one")
     ap.add_argument("--solve-mode", choices=("fixed", "ticket", "levels"), default="fixed",
-                    help="triangular solves: persistent launch with fixed item order (default), with "
-                         "ticket order, or one launch per level")
+                    help="triangular solves: one persistent launch per triangle (default; ticket: the same) "
+                         "or one launch per level")
     ap.add_argument("--path", choices=("fused", "separate"), default="fused",
                     help="grid: kkt_refactor_refine (forward substitution beside the refactorization, "
                          "default) or kkt_refactor followed by kkt_refine; the results are the same bit for bit")
@@ -459,11 +459,11 @@ def main():
     }
     tname = "float" if fp32 else "double"
     kernel_of = {"refactor_large": f"k_refactor_wide<WideCfg<{tname}, 512, 2, 256, 32, 4> >",
-                 "refactor_medium": f"k_refactor_wide<WideCfg<{tname}, 256, 4, 128, 16, 2> >",
+                 "refactor_medium": f"k_refactor_wave<{tname}>/k_refactor_wide<WideCfg<{tname}, 256, 4, 128, 16, 2> >",
                  "refactor_w256": f"k_refactor_wide<WideCfg<{tname}, 256, 2, 128, 32, 4> >",
                  "refactor_small": "k_refactor_small",
                  "lsolve": "k_lsolve_persistent", "usolve": "k_usolve_persistent", "to_csr": "k_to_csr",
-                 "update": "k_set_call..k_max_parts", "residual": "k_residual/k_spmv", "krylov": "krylov"}
+                 "update": "k_set_call..k_norms", "residual": "k_residual/k_spmv", "krylov": "krylov"}
     ranked = sorted((v[1], k) for k, v in prof.items())
     dom = ranked[-1][1]
     launches, ms = prof[dom]

@@ -230,7 +230,8 @@ int kkt_refactor_status(kkt_handle *h, int64_t *perturbed, hipStream_t stream);
 
 /* Triangular solves (Algorithm 1, triangular solve), no refinement:
  * x = Q C (L U)^-1 P R b.  d_b, d_x: device FP64, column j at offset j*ld, nrhs columns,
- * ld >= n; d_x may equal d_b.  Asynchronous.  Errors: ARG, STATE, DEVICE. */
+ * ld >= n; d_x may equal d_b.  With persistent solves up to 8 columns share a launch per
+ * triangle, each with the result it has alone.  Asynchronous.  Errors: ARG, STATE, DEVICE. */
 int kkt_solve(kkt_handle *h, const double *d_b, double *d_x, int32_t nrhs, int64_t ld,
               hipStream_t stream);
 
@@ -253,9 +254,10 @@ int kkt_refine(kkt_handle *h, const double *d_b, double *d_x, int32_t nrhs, int6
  * kkt_refine(h, d_b, d_x, 1, n, info), with the same results bit for bit (factors, x and
  * info).  The forward substitution of the first solve rides in the refactorization's level
  * launches: each forward level runs in the first launch after the columns its rows read are
- * factored and copied, the last levels after the last launch (replayed from a second graph
- * recorded at the first call after kkt_bind when opts.graph_refactor is set; launched one by
- * one without graphs, with the profiler on or on a capturing stream).  d_values as for
+ * factored and copied, the last levels after the last launch; the backward substitution, the
+ * residual and the report of both to the host follow in the same graph (a second one, recorded
+ * at the first call after kkt_bind when opts.graph_refactor is set; launched one by one
+ * without graphs, with the profiler on or on a capturing stream).  d_values as for
  * kkt_refactor (BORROWED); d_b, d_x: device FP64[n], d_x may equal d_b; info: host
  * kkt_info[1] (may be NULL).  Waits for completion.  Returns what kkt_refine returns; a
  * failed factorization (ERR_NONFINITE, ERR_DEVICE) is reported with info = {0, error, inf,
@@ -337,8 +339,11 @@ int kkt_batch_refactor(kkt_batch *b, const double *const *d_values, hipStream_t 
 
 /* kkt_refine of every handle of the batch with one right-hand side each: d_b, d_x host
  * arrays of count device pointers (FP64[n] of that handle), info host kkt_info[count] (may
- * be NULL).  Up to 8 handles are refined at once, each by a host thread on a stream of the
- * batch ordered after the caller's stream.  Waits.  Returns the first error, else the worst
+ * be NULL).  The first solves and residuals of all handles run in one launch per triangle;
+ * handles that need FGMRES steps then (or all of them, when the solves cannot be merged: a
+ * failed factorization, solutions over right-hand sides, the profiler on, level solves) are
+ * refined up to 8 at once, each by a host thread on a stream of the batch ordered after the
+ * caller's stream.  Waits.  Returns the first error, else the worst
  * warning. */
 int kkt_batch_refine(kkt_batch *b, const double *const *d_b, double *const *d_x, kkt_info *info,
                      hipStream_t stream);
@@ -404,7 +409,7 @@ void kkt_server_destroy(kkt_server *s);
 #define KKT_PROF_UPDATE 0          /* equilibration, norms, value gather, counters */
 #define KKT_PROF_REFACTOR_LARGE 1  /* 512-thread level launches: wide panel items up to 32 columns
                                     * (LDS-staged, matrix cores) and the level's narrow items */
-#define KKT_PROF_REFACTOR_SMALL 2  /* narrow-only level launches (16 lanes per item) */
+#define KKT_PROF_REFACTOR_SMALL 2  /* narrow-only level launches (4 or 16 lanes per item) */
 #define KKT_PROF_TO_CSR 3          /* row-ordered copy of the factors */
 #define KKT_PROF_LSOLVE 4          /* forward substitution (and its Jacobi sweeps; with
                                     * kkt_refactor_refine only its last levels and the set-up,
@@ -413,7 +418,8 @@ void kkt_server_destroy(kkt_server *s);
 #define KKT_PROF_RESIDUAL 6        /* residual, products with A */
 #define KKT_PROF_KRYLOV 7          /* FGMRES vector kernels */
 #define KKT_PROF_REFACTOR_MEDIUM 8 /* 256-thread level launches: wide items of panels up to 16
-                                    * columns and the level's narrow items */
+                                    * columns (a wavefront each, or a block each on levels with
+                                    * panels of more than 96 rows) and the level's narrow items */
 #define KKT_PROF_REFACTOR_W256 9   /* 256-thread level launches: wide items of panels up to 32
                                     * columns with factored panels of at most 256 rows, and the
                                     * level's narrow items */

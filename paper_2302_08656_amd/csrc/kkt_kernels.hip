@@ -4,9 +4,10 @@
 // row/column equilibration (the analysis stage equilibrates, Section II) and a gather of
 // the scaled values into the combined L+U storage.
 // Refactorization (Algorithm 1, refactor without pivoting): one launch per panel level;
-// see kkt_schedule.cpp for the schedule.  Each work item is one 64-lane wavefront.
-// Triangular solves (Algorithm 1, triangular solve) on a row-ordered copy of L+U, one
-// launch per panel level; residuals and Krylov vector work for the refinement.
+// see kkt_schedule.cpp for the schedule.  A work item runs on 4 or 16 lanes, on a wavefront or
+// on a block, by the widths and lengths of its panels.
+// Triangular solves (Algorithm 1, triangular solve) on a row-ordered copy of L+U, one launch
+// per triangle; residuals and Krylov vector work for the refinement.
 #include <hip/hip_runtime.h>
 
 #include <cstddef>
@@ -524,16 +525,6 @@ __global__ __launch_bounds__(256) void k_to_csr(CopyRanges c, const int32_t *__r
 
 // ---------------------------------------------------------------------------------------
 // refactorization
-
-// first index in [lo, hi) whose row >= key
-__device__ __forceinline__ int lower_bound_row(const int32_t *__restrict__ rowidx, int lo, int hi, int key) {
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (rowidx[mid] < key) lo = mid + 1;
-        else hi = mid;
-    }
-    return lo;
-}
 
 constexpr int kBlock = 256;   // threads of the elementwise, small-item and solve blocks
 

@@ -23,7 +23,7 @@ namespace {
 struct Dev {
     int32_t *a_rowptr, *a_colind;
     int2 *lu_src;       // per factor slot: {CSR position of its entry of A or -1, that entry's row}
-    int32_t *colptr, *rowidx, *ulen, *pan_start, *pan_r;
+    int32_t *colptr, *pan_start, *pan_r;
     int32_t *f_rel, *ldiag;
     int4 *itemrec, *pair8;
     unsigned long long *pcount;
@@ -129,8 +129,6 @@ void carve(const kkt_handle *h, char *base, Dev &d, size_t *bytes) {
     d.a_colind = c.take<int32_t>(na);
     d.lu_src = c.take<int2>(std::max<size_t>(1, nlu));
     d.colptr = c.take<int32_t>(n + 1);
-    d.rowidx = c.take<int32_t>(nlu);
-    d.ulen = c.take<int32_t>(n);
     d.pan_start = c.take<int32_t>(g.pan_start.size());
     d.pan_r = c.take<int32_t>(g.pan_r.size());
     d.itemrec = c.take<int4>(std::max<size_t>(4, g.itemrec.size() / 4));
@@ -955,7 +953,11 @@ int kkt_workspace_bytes(const kkt_handle *h, int32_t max_nrhs, size_t *bytes) {
 // Static device scratch of kkt_bind_scratch, one copy per device (each holds it until the
 // process ends).  Host code never passes `scratch` itself to the device: its device address
 // is taken once per device with hipGetSymbolAddress and kept in g_scratch_ptr.
-static __device__ __align__(256) char scratch[KKT_SCRATCH_BYTES];
+// The first pair's record inside the item records (16 bytes an item) is not charged to the
+// limit: triangular and banded patterns have so many items that it outweighs what the
+// workspace no longer holds, and they are to fit as before.
+constexpr size_t kScratchSlack = (size_t)4 << 20;
+static __device__ __align__(256) char scratch[KKT_SCRATCH_BYTES + kScratchSlack];
 
 namespace {
 
@@ -1040,8 +1042,6 @@ int bind_common(kkt_handle *h, char *ws, size_t bytes, int32_t max_nrhs, hipStre
     rc |= upload(d.a_colind, s.a_colind, stream);
     rc |= upload(reinterpret_cast<int32_t *>(d.lu_src), g.lu_src, stream);
     rc |= upload(d.colptr, g.colptr32, stream);
-    rc |= upload(d.rowidx, s.rowidx, stream);
-    rc |= upload(d.ulen, s.ulen, stream);
     rc |= upload(d.pan_start, g.pan_start, stream);
     rc |= upload(d.pan_r, g.pan_r, stream);
     rc |= upload(reinterpret_cast<int32_t *>(d.itemrec), g.itemrec, stream);
@@ -1088,7 +1088,8 @@ int kkt_bind_scratch(kkt_handle *h, int32_t max_nrhs, hipStream_t stream) {
     size_t need = 0;
     Dev probe{};
     carve(h, nullptr, probe, &need);
-    if (need > KKT_SCRATCH_BYTES) return KKT_ERR_NOMEM;   // beyond the static array
+    const size_t first = 16 * h->sch.f_item_panel.size();
+    if (need > KKT_SCRATCH_BYTES + std::min(first, kScratchSlack)) return KKT_ERR_NOMEM;   // beyond the static array
     int dev = -1;
     HIPCHK(hipGetDevice(&dev));
     if (dev < 0 || dev >= kMaxDevices) return KKT_ERR_DEVICE;
@@ -1110,7 +1111,8 @@ int kkt_bind_scratch(kkt_handle *h, int32_t max_nrhs, hipStream_t stream) {
     }
     g_scratch_owner[dev] = nullptr;
     h->on_scratch = false;
-    const int rc = bind_common(h, static_cast<char *>(g_scratch_ptr[dev]), KKT_SCRATCH_BYTES, max_nrhs, stream, true);
+    const int rc = bind_common(h, static_cast<char *>(g_scratch_ptr[dev]), sizeof(scratch), max_nrhs,
+                               stream, true);
     if (rc == KKT_OK) g_scratch_owner[dev] = h;
     return rc;
 }
