@@ -208,7 +208,8 @@ int kkt_bind(kkt_handle *h, void *d_workspace, size_t bytes, int32_t max_nrhs,
  * unbinds the previous one (its later calls return STATE) and overwrites the array, so
  * calls of handles that use it must not overlap in time (they race on one array); the
  * caller orders them.  Results are bitwise identical to the same handle bound by kkt_bind.
- * Waits for the upload.  Errors: ARG, NOMEM (kkt_workspace_bytes exceeds KKT_SCRATCH_BYTES),
+ * Waits for the upload.  Errors: ARG, NOMEM (kkt_workspace_bytes exceeds KKT_SCRATCH_BYTES, by
+ * more than a few MiB of item records where a pattern has unusually many),
  * STATE (handle already on another device), DEVICE. */
 int kkt_bind_scratch(kkt_handle *h, int32_t max_nrhs, hipStream_t stream);
 

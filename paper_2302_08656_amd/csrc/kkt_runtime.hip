@@ -953,9 +953,10 @@ int kkt_workspace_bytes(const kkt_handle *h, int32_t max_nrhs, size_t *bytes) {
 // Static device scratch of kkt_bind_scratch, one copy per device (each holds it until the
 // process ends).  Host code never passes `scratch` itself to the device: its device address
 // is taken once per device with hipGetSymbolAddress and kept in g_scratch_ptr.
-// The first pair's record inside the item records (16 bytes an item) is not charged to the
-// limit: triangular and banded patterns have so many items that it outweighs what the
-// workspace no longer holds, and they are to fit as before.
+// It is larger than the limit by kScratchSlack: triangular and banded patterns have so many
+// items that the first pair's record inside each (16 bytes) outweighs the index arrays of the
+// factor that the device no longer holds, and a system whose workspace fitted with those arrays
+// and without that record still binds.
 constexpr size_t kScratchSlack = (size_t)4 << 20;
 static __device__ __align__(256) char scratch[KKT_SCRATCH_BYTES + kScratchSlack];
 
@@ -1089,7 +1090,9 @@ int kkt_bind_scratch(kkt_handle *h, int32_t max_nrhs, hipStream_t stream) {
     Dev probe{};
     carve(h, nullptr, probe, &need);
     const size_t first = 16 * h->sch.f_item_panel.size();
-    if (need > KKT_SCRATCH_BYTES + std::min(first, kScratchSlack)) return KKT_ERR_NOMEM;   // beyond the static array
+    const size_t indices = sizeof(int32_t) * ((size_t)h->sym.nnz_lu() + h->sym.n);
+    if (need > KKT_SCRATCH_BYTES && (need + indices - first > KKT_SCRATCH_BYTES || need > sizeof(scratch)))
+        return KKT_ERR_NOMEM;   // beyond the static array
     int dev = -1;
     HIPCHK(hipGetDevice(&dev));
     if (dev < 0 || dev >= kMaxDevices) return KKT_ERR_DEVICE;
