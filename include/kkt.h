@@ -327,8 +327,11 @@ int kkt_autotune(kkt_handle *h, const double *d_values, int32_t reps, kkt_tuning
 typedef struct kkt_batch kkt_batch;
 
 /* handles: host array of count distinct bound handles.  The batch keeps pointers to them
- * and to their workspaces: a handle must stay alive and bound to the same workspace while
- * the batch is used (calls return STATE otherwise).  Allocates a small device table.
+ * and to their workspaces: a handle must stay alive, bound to the same workspace and with the
+ * same schedule while the batch is used.  Unbound, bound elsewhere or retuned (kkt_set_tuning,
+ * kkt_autotune, also when bound to the same address again), kkt_batch_refactor returns STATE;
+ * kkt_batch_refine refines the handles as they now are, each alone.  Allocates small device
+ * tables.
  * Errors: ARG (null, duplicate, mixed device or precision), STATE (unbound), NOMEM, DEVICE. */
 int kkt_batch_create(kkt_handle *const *handles, int32_t count, kkt_batch **out);
 

@@ -196,7 +196,8 @@ constexpr int kBatchRefineThreads = 8;
 
 struct kkt_batch {
     std::vector<kkt_handle *> hs;
-    std::vector<char *> ws;        // each handle's workspace when the batch was made
+    std::vector<char *> ws;        // each handle's workspace and schedule when the batch was made:
+    std::vector<uint64_t> sch_id;  // its device tables point into that workspace, laid out for that schedule
     int device = -1;
     bool fp32 = false;
     char *dmem = nullptr;          // device: systems, shares, value-pointer table
@@ -378,6 +379,13 @@ void batch_free(kkt_batch *b) {
     delete b;
 }
 
+// the batch's tables still describe handle i: not unbound, bound elsewhere or given another
+// schedule since (a rebuilt schedule lays the same workspace address out anew)
+bool batch_tables_hold(const kkt_batch *b, int i) {
+    const kkt_handle *h = b->hs[i];
+    return h->bound && h->ws == b->ws[i] && h->sch_id == b->sch_id[i];
+}
+
 // (handle, item) of every handle's solve items, level by level
 void batch_order(const kkt_batch *b, bool fwd, std::vector<int2> &ord) {
     size_t nlev = 0;
@@ -438,7 +446,10 @@ int kkt_batch_create(kkt_handle *const *handles, int32_t count, kkt_batch **out)
     kkt_batch *b = new (std::nothrow) kkt_batch;
     if (!b) return KKT_ERR_NOMEM;
     b->hs.assign(handles, handles + count);
-    for (auto *h : b->hs) b->ws.push_back(h->ws);
+    for (auto *h : b->hs) {
+        b->ws.push_back(h->ws);
+        b->sch_id.push_back(h->sch_id);
+    }
     b->device = handles[0]->device;
     b->fp32 = handles[0]->opts.factor_precision == KKT_FP32;
     DeviceGuard dg(b->device);
@@ -551,7 +562,7 @@ int kkt_batch_refactor(kkt_batch *b, const double *const *d_values, hipStream_t 
     const int count = (int)b->hs.size();
     for (int i = 0; i < count; ++i) {
         if (!d_values[i]) return KKT_ERR_ARG;
-        if (!b->hs[i]->bound || b->hs[i]->ws != b->ws[i]) return KKT_ERR_STATE;   // unbound or rebound since
+        if (!batch_tables_hold(b, i)) return KKT_ERR_STATE;
     }
     DeviceGuard dg(b->device);
     if (!dg.ok) return KKT_ERR_DEVICE;
@@ -603,12 +614,12 @@ int kkt_batch_refine(kkt_batch *b, const double *const *d_b, double *const *d_x,
     if (!dg.ok) return KKT_ERR_DEVICE;
     std::vector<int> rcs(count, KKT_OK);
     std::vector<kkt_info> infs(count);
-    // the first solves of all handles together, where every handle can take part: refactored, on
-    // the workspace of the batch, not profiled, solving in place of nothing, its factors sound
+    // the first solves of all handles together, where every handle can take part: refactored, as
+    // the batch's tables describe it, not profiled, solving in place of nothing, its factors sound
     bool merged = true;
     for (int i = 0; i < count; ++i) {
         const kkt_handle *h = b->hs[i];
-        merged &= h->bound && h->factored && h->ws == b->ws[i] && !h->prof && h->opts.persistent_solve != 0;
+        merged &= batch_tables_hold(b, i) && h->factored && !h->prof && h->opts.persistent_solve != 0;
         for (int j = 0; j < count && merged; ++j) merged &= d_b[i] != d_x[j] && (i == j || d_x[i] != d_x[j]);
     }
     std::vector<char> solved(count, 0);

@@ -78,6 +78,7 @@ struct kkt_handle {
     kkt_opts opts{};
     Symbolic sym;
     Schedule sch;
+    uint64_t sch_id = 0;   // raised whenever sch is replaced: arrays laid out for it are then stale
     bool bound = false;
     bool factored = false;
     int device = -1;
@@ -1381,6 +1382,7 @@ int set_schedule(kkt_handle *h, const SchedParams &p) {
     }
     if (rc != KKT_OK) return rc;
     h->sch = std::move(g);
+    ++h->sch_id;
     return KKT_OK;
 }
 
