@@ -1955,6 +1955,8 @@ __device__ __forceinline__ double sdot(const SolveArgs<TF> &a, const double *v, 
 #pragma unroll
                 for (int k = 4; k < B; ++k) vv[k] = 0.0;
             }
+#pragma unroll
+            for (int k = 1; k < B; ++k) vv[k] = k < rem ? vv[k] : 0.0;   // 0 * inf is not 0
         }
 #pragma unroll
         for (int k0 = 0; k0 < B; k0 += 4) {
