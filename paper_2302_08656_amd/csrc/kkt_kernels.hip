@@ -2493,7 +2493,6 @@ __device__ __forceinline__ void residual_body(int blk, int nblk, int n, const in
                                               double *__restrict__ res, double *__restrict__ part,
                                               ResNorms *acc) {
     __shared__ double red[3][4];
-    const double qnan = __longlong_as_double(0x7ff8000000000000LL);
     double rn = 0.0, xn = 0.0, bn = 0.0;
     const int gl = threadIdx.x & 7;
     for (int i0 = ((blk * blockDim.x + threadIdx.x) >> 3) * kRowsPerGroup; i0 < n;
@@ -2527,8 +2526,8 @@ __device__ __forceinline__ void residual_body(int blk, int nblk, int n, const in
         if (own) {
             const double ri = bi - mine;
             if (res) res[i] = ri;
-            rn = isnan(ri) ? qnan : fmax(rn, fabs(ri));
-            xn = isnan(xi) ? qnan : fmax(xn, fabs(xi));
+            rn = max_nan(rn, fabs(ri));   // a lane has several rows: a NaN stays
+            xn = max_nan(xn, fabs(xi));
             bn = fmax(bn, fabs(bi));
         }
     }
