@@ -232,7 +232,8 @@ int kkt_refactor_status(kkt_handle *h, int64_t *perturbed, hipStream_t stream);
 /* Triangular solves (Algorithm 1, triangular solve), no refinement:
  * x = Q C (L U)^-1 P R b.  d_b, d_x: device FP64, column j at offset j*ld, nrhs columns,
  * ld >= n; d_x may equal d_b.  With persistent solves up to 8 columns share a launch per
- * triangle, each with the result it has alone.  Asynchronous.  Errors: ARG, STATE, DEVICE. */
+ * triangle, each with the result it has alone; where d_x overlaps d_b otherwise, the columns
+ * are solved one after the other.  Asynchronous.  Errors: ARG, STATE, DEVICE. */
 int kkt_solve(kkt_handle *h, const double *d_b, double *d_x, int32_t nrhs, int64_t ld,
               hipStream_t stream);
 
@@ -246,6 +247,8 @@ int kkt_solve_approx(kkt_handle *h, const double *d_b, double *d_x, int32_t nrhs
 /* Solve followed by FGMRES(m) iterative refinement with FP64 residuals on the original A
  * (Algorithm 1: the solve is always followed by iterative refinement; Section V: a
  * configurable refinement).  Stops when berr <= berr_tol or after max_iters Arnoldi steps.
+ * d_x may equal d_b; shifted by whole columns over d_b, column j is solved and refined before
+ * column j + 1 is begun, so a right-hand side that was used already may be overwritten.
  * info: host kkt_info[nrhs] (may be NULL).  Waits for completion.  Returns OK,
  * WARN_NOT_CONVERGED (some column missed the target), or an error. */
 int kkt_refine(kkt_handle *h, const double *d_b, double *d_x, int32_t nrhs, int64_t ld,

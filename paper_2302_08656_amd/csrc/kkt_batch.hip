@@ -386,6 +386,12 @@ bool batch_tables_hold(const kkt_batch *b, int i) {
     return h->bound && h->ws == b->ws[i] && h->sch_id == b->sch_id[i];
 }
 
+// whether na doubles at a and nb doubles at b share memory
+bool arrays_overlap(const double *a, int64_t na, const double *b, int64_t nb) {
+    const uintptr_t p = reinterpret_cast<uintptr_t>(a), q = reinterpret_cast<uintptr_t>(b);
+    return p < q + sizeof(double) * nb && q < p + sizeof(double) * na;
+}
+
 // (handle, item) of every handle's solve items, level by level
 void batch_order(const kkt_batch *b, bool fwd, std::vector<int2> &ord) {
     size_t nlev = 0;
@@ -615,12 +621,16 @@ int kkt_batch_refine(kkt_batch *b, const double *const *d_b, double *const *d_x,
     std::vector<int> rcs(count, KKT_OK);
     std::vector<kkt_info> infs(count);
     // the first solves of all handles together, where every handle can take part: refactored, as
-    // the batch's tables describe it, not profiled, solving in place of nothing, its factors sound
+    // the batch's tables describe it, not profiled, its solution over no right-hand side
+    // and no other solution, its factors sound
     bool merged = true;
     for (int i = 0; i < count; ++i) {
         const kkt_handle *h = b->hs[i];
         merged &= batch_tables_hold(b, i) && h->factored && !h->prof && h->opts.persistent_solve != 0;
-        for (int j = 0; j < count && merged; ++j) merged &= d_b[i] != d_x[j] && (i == j || d_x[i] != d_x[j]);
+        for (int j = 0; j < count && merged; ++j) {
+            const int n = h->sym.n, nj = b->hs[j]->sym.n;
+            merged &= !arrays_overlap(d_b[i], n, d_x[j], nj) && (i == j || !arrays_overlap(d_x[i], n, d_x[j], nj));
+        }
     }
     std::vector<char> solved(count, 0);
     if (merged) {

@@ -340,11 +340,25 @@ int enqueue_solve(kkt_handle *h, const double *b, double *x, hipStream_t s, bool
     return by_precision(h, [&](auto tag) { return enqueue_solve_t<decltype(tag)>(h, b, x, s, forward); });
 }
 
+// whether x's column j shares memory with b's column i for some |i - j| < ncol (columns of n
+// doubles at stride ld)
+bool columns_overlap(const double *b, const double *x, int n, int64_t ld, int ncol) {
+    const int64_t d = static_cast<int64_t>(reinterpret_cast<uintptr_t>(x) - reinterpret_cast<uintptr_t>(b));
+    const int64_t col = (int64_t)sizeof(double) * n, step = (int64_t)sizeof(double) * ld;
+    for (int k = 1 - ncol; k < ncol; ++k)
+        if (d + k * step < col && d + k * step > -col) return true;
+    return false;
+}
+
 // The columns that one launch per triangle can solve: the buffers of those after the first lie
-// in the Krylov basis V, the residuals' block maxima in Z (both unused until FGMRES steps).
-int solve_cols(const kkt_handle *h, int nrhs) {
+// in the Krylov basis V, the residuals' block maxima in Z (both unused until FGMRES steps).  All
+// solutions of a launch are written before the residuals read b, so columns of x that lie over
+// columns of b go one after the other, as a loop over the columns has them.  x null: one that
+// overlaps nothing.
+int solve_cols(const kkt_handle *h, int nrhs, const double *b, const double *x, int64_t ld) {
     const int m = h->opts.gmres_restart;
     if (h->opts.persistent_solve == 0) return 1;
+    if (x && columns_overlap(b, x, h->sym.n, ld, std::min(nrhs, kMaxCols))) return 1;
     const int c = std::min(std::min(nrhs, kMaxCols), 1 + (m + 1) / 5);
     return (int64_t)3 * norm_blocks(h->sym.n) * c <= (int64_t)m * h->sym.n ? c : 1;
 }
@@ -1257,7 +1271,8 @@ int kkt_solve(kkt_handle *h, const double *d_b, double *d_x, int32_t nrhs, int64
     if (!h->factored) return KKT_ERR_STATE;
     DeviceGuard dg(h->device);
     if (!dg.ok) return KKT_ERR_DEVICE;
-    const int nc = solve_cols(h, nrhs);
+    // in place (x = b): the launches' set-up has read every right-hand side before x is written
+    const int nc = solve_cols(h, nrhs, d_b, d_b == d_x ? nullptr : d_x, ld);
     for (int32_t j = 0; j < nrhs; j += nc) {
         const int rc = enqueue_solve_cols(h, d_b + (size_t)j * ld, d_x + (size_t)j * ld, std::min(nc, nrhs - j), ld,
                                           stream);
@@ -1300,8 +1315,8 @@ int kkt_refine(kkt_handle *h, const double *d_b, double *d_x, int32_t nrhs, int6
     int worst = KKT_OK;
     // columns beside each other: their first solves and residuals together, then FGMRES column by
     // column for those short of the target.  Right-hand sides that the solutions overwrite go
-    // one by one through the saved copy.
-    const int nc = d_b == d_x ? 1 : solve_cols(h, nrhs);
+    // one by one (in place: through the saved copy).
+    const int nc = solve_cols(h, nrhs, d_b, d_x, ld);
     const int32_t jm = nc > 1 ? nrhs : 0;
     for (int32_t j0 = 0; j0 < jm; j0 += nc) {
         const int c1 = std::min(nc, nrhs - j0);
