@@ -350,8 +350,8 @@ int kkt_batch_refactor(kkt_batch *b, const double *const *d_values, hipStream_t 
  * handles that need FGMRES steps then (or all of them, when the solves cannot be merged: a
  * failed factorization, solutions over right-hand sides, the profiler on, level solves) are
  * refined up to 8 at once, each by a host thread on a stream of the batch ordered after the
- * caller's stream.  Waits.  Returns the first error, else the worst
- * warning. */
+ * caller's stream.  Waits.  Returns the first error, else the worst warning; info[i] of a
+ * handle that failed holds its error as status and an infinite berr. */
 int kkt_batch_refine(kkt_batch *b, const double *const *d_b, double *const *d_x, kkt_info *info,
                      hipStream_t stream);
 

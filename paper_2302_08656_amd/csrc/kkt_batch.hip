@@ -648,17 +648,9 @@ int kkt_batch_refine(kkt_batch *b, const double *const *d_b, double *const *d_x,
         if (!rc) rc = batch_read(b, stream);
         if (rc) return rc;
         for (int i = 0; i < count; ++i) {
-            const DevStatus &st = b->h_res[i].st;
-            const ResNorms &rn = b->h_res[i].rn;
-            infs[i].perturbed_pivots = (int64_t)st.perturbed;
-            if (st.abort) {
-                rcs[i] = KKT_ERR_DEVICE;
-                solved[i] = 2;
-                continue;
-            }
-            const double den = st.anorm * rn.xnorm + rn.bnorm;
-            infs[i].berr = den == 0.0 ? (rn.rnorm == 0.0 ? 0.0 : INFINITY) : rn.rnorm / den;
-            solved[i] = infs[i].berr <= b->hs[i]->opts.berr_tol ? 2 : 1;   // 2: done
+            const int rc1 = first_info(b->h_res[i].st, b->h_res[i].rn, b->hs[i]->opts.berr_tol, &infs[i]);
+            rcs[i] = std::min(rc1, KKT_OK);
+            solved[i] = rc1 == KKT_WARN_NOT_CONVERGED ? 1 : 2;   // 2: done
         }
     }
     // the rest by worker threads on streams that start after everything enqueued so far
@@ -670,13 +662,14 @@ int kkt_batch_refine(kkt_batch *b, const double *const *d_b, double *const *d_x,
             (void)hipSetDevice(b->device);
             for (int i; (i = next.fetch_add(1)) < count;) {
                 if (solved[i] == 2) continue;
+                const int64_t pert = infs[i].perturbed_pivots;
                 if (solved[i] == 0) {
                     rcs[i] = kkt_refine(b->hs[i], d_b[i], d_x[i], 1, b->hs[i]->sym.n, &infs[i], st);
-                    continue;
+                } else {
+                    rcs[i] = fgmres_column(b->hs[i], d_b[i], d_x[i], &infs[i], st, kSolved);
+                    infs[i].perturbed_pivots = pert;
                 }
-                const int64_t pert = infs[i].perturbed_pivots;
-                rcs[i] = fgmres_column(b->hs[i], d_b[i], d_x[i], &infs[i], st, kSolved);
-                infs[i].perturbed_pivots = pert;
+                if (rcs[i] < 0) info_error(rcs[i], pert, &infs[i]);
             }
         };
         std::vector<std::thread> pool;

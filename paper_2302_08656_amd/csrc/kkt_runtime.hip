@@ -656,9 +656,7 @@ int residual_berr(kkt_handle *h, double *berr, double *den, hipStream_t s, DevSt
     for (int c = 0; c < ncol; ++c) {
         ResNorms rn;
         std::memcpy(&rn, reinterpret_cast<const char *>(h->h_small) + at + c * sizeof(rn), sizeof(rn));
-        den[c] = st.anorm * rn.xnorm + rn.bnorm;
-        if (den[c] == 0.0) berr[c] = rn.rnorm == 0.0 ? 0.0 : INFINITY;
-        else berr[c] = rn.rnorm / den[c];
+        berr[c] = backward_error(st, rn, &den[c]);
     }
     return KKT_OK;
 }
