@@ -199,7 +199,7 @@ int kkt_bind(kkt_handle *h, void *d_workspace, size_t bytes, int32_t max_nrhs,
 
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc): kkt_bind with the workspace taken from
- * the library's own static device array of KKT_SCRATCH_BYTES bytes instead of caller
+ * the library's own static device array (KKT_SCRATCH_BYTES and some room) instead of caller
  * memory.  This call allocates nothing (no device or pinned host memory, no stream, event
  * or graph); later calls on the handle allocate nothing either: its refactorizations launch
  * their levels one by one instead of recording a graph, and small read-backs go through a
@@ -208,9 +208,11 @@ int kkt_bind(kkt_handle *h, void *d_workspace, size_t bytes, int32_t max_nrhs,
  * unbinds the previous one (its later calls return STATE) and overwrites the array, so
  * calls of handles that use it must not overlap in time (they race on one array); the
  * caller orders them.  Results are bitwise identical to the same handle bound by kkt_bind.
- * Waits for the upload.  Errors: ARG, NOMEM (kkt_workspace_bytes exceeds KKT_SCRATCH_BYTES, by
- * more than a few MiB of item records where a pattern has unusually many),
- * STATE (handle already on another device), DEVICE. */
+ * Waits for the upload.  Errors: ARG, NOMEM (does not fit; nothing is changed then), STATE
+ * (handle already on another device), DEVICE.  Every system with kkt_workspace_bytes up to
+ * KKT_SCRATCH_BYTES fits.  The array is 7 MiB larger, for patterns with very many work items
+ * (triangular and wide banded ones): theirs fit when the workspace without 16 bytes of each
+ * item's record, and with 4 more for each entry and row of the factor, is within the limit. */
 int kkt_bind_scratch(kkt_handle *h, int32_t max_nrhs, hipStream_t stream);
 
 /* Value update and refactorization without pivoting (Algorithm 1, update the factor

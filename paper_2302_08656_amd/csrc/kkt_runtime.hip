@@ -966,11 +966,13 @@ int kkt_workspace_bytes(const kkt_handle *h, int32_t max_nrhs, size_t *bytes) {
 // Static device scratch of kkt_bind_scratch, one copy per device (each holds it until the
 // process ends).  Host code never passes `scratch` itself to the device: its device address
 // is taken once per device with hipGetSymbolAddress and kept in g_scratch_ptr.
-// It is larger than the limit by kScratchSlack: triangular and banded patterns have so many
-// items that the first pair's record inside each (16 bytes) outweighs the index arrays of the
-// factor that the device no longer holds, and a system whose workspace fitted with those arrays
-// and without that record still binds.
-constexpr size_t kScratchSlack = (size_t)4 << 20;
+// The limit is a workspace of KKT_SCRATCH_BYTES without the first pair's record inside each item
+// (16 bytes an item) and with the factor's index arrays, which the device no longer holds (4 bytes
+// an entry and row), or one of KKT_SCRATCH_BYTES as it is: what fitted before the items carried
+// that record still fits.  Patterns with an item for nearly every entry of the factor (dense or
+// wide banded triangles) grow most by the change: 16 - 4 bytes on the 112 or more that such an
+// entry takes with its item, pair, values and copies, under 11 %, so that 7 MiB more hold them.
+constexpr size_t kScratchSlack = (size_t)7 << 20;
 static __device__ __align__(256) char scratch[KKT_SCRATCH_BYTES + kScratchSlack];
 
 namespace {
