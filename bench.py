@@ -37,9 +37,9 @@ def parse():
     ap.add_argument("--precision", choices=("fp64", "fp32"), default=None,
                     help="factor storage and refactorization precision (refinement stays FP64); default "
                          "fp64 for the grid workloads, fp32 for the batched one")
-    ap.add_argument("--solve-mode", choices=("fixed", "ticket", "levels"), default="fixed",
-                    help="triangular solves: one persistent launch per triangle (default; ticket: the same) "
-                         "or one launch per level")
+    ap.add_argument("--solve-mode", choices=("persistent", "fixed", "ticket", "levels"), default="persistent",
+                    help="triangular solves: one persistent launch per triangle (default; fixed and ticket are "
+                         "older names of it) or one launch per level")
     ap.add_argument("--path", choices=("fused", "separate"), default="fused",
                     help="grid: kkt_refactor_refine (forward substitution beside the refactorization, "
                          "default) or kkt_refactor followed by kkt_refine; the results are the same bit for bit")
@@ -383,7 +383,7 @@ def main():
     fp32 = args.precision == "fp32"
     sk = K.KKTSolver(q.n, q.rowptr, q.colind, vals[0], approx_sweeps=args.approx_sweeps,
                      factor_precision=K.FP32 if fp32 else K.FP64,
-                     persistent_solve={"fixed": 1, "ticket": 2, "levels": 0}[args.solve_mode])
+                     persistent_solve={"levels": 0, "ticket": 2}.get(args.solve_mode, 1))
     t_analyze = time.perf_counter() - t0
     st = sk.stats
     print(f"[bench] analyze {t_analyze:.2f}s nnz_lu={st['nnz_lu']} levels={st['levels_f']} "
@@ -501,7 +501,7 @@ def main():
                    "timed_systems": (f"all {T}" if len(timed) == T else timed),
                    "refinement_preconditioner": (f"{args.approx_sweeps} Jacobi sweeps per triangle"
                                                  if args.approx_sweeps else "exact triangular solves"),
-                   "solve_mode": args.solve_mode, "path": args.path},
+                   "solve_mode": "levels" if args.solve_mode == "levels" else "persistent", "path": args.path},
         "p50_ms": round(nearest_rank(lat, 50), 4), "p99_ms": round(nearest_rank(lat, 99), 4),
         "failures": fails, "fgmres_iters_mean": round(float(np.mean(iters)), 3),
         "berr_max": float(np.max(berrs)),

@@ -325,9 +325,9 @@ int kkt_autotune(kkt_handle *h, const double *d_values, int32_t reps, kkt_tuning
 /* Batched refactorization (many same- or different-pattern systems per call): a batch
  * groups bound handles of one device and one factor precision; kkt_batch_refactor then
  * does for all of them what kkt_refactor does for one, with one launch per dependency
- * level across the batch (each handle's share of a launch runs exactly the blocks of its
- * own launch, so every result is bitwise the one of kkt_refactor alone), the value update
- * merged likewise, and all launches of a step recorded at the first call into one HIP
+ * level across the batch (each handle has a share of every launch, which computes what the
+ * handle's own launch computes, sometimes in blocks of another size, so every result is
+ * bitwise the one of kkt_refactor alone), the value update merged likewise, and all launches of a step recorded at the first call into one HIP
  * graph that later calls replay. */
 typedef struct kkt_batch kkt_batch;
 

@@ -18,7 +18,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libkkt.so")
 
 OK, WARN_PIVOT_PERTURBED, WARN_NOT_CONVERGED = 0, 1, 2
-# bytes of the static device array behind KKTSolver.bind_scratch (KKT_SCRATCH_BYTES)
+# workspace up to which KKTSolver.bind_scratch takes every system (KKT_SCRATCH_BYTES)
 SCRATCH_BYTES = 64 << 20
 FP64, FP32 = 0, 1   # factor_precision
 ERR_ARG, ERR_PATTERN, ERR_SINGULAR, ERR_NONFINITE, ERR_STATE, ERR_NOMEM, ERR_DEVICE, ERR_SCHEDULE = \
@@ -434,7 +434,7 @@ class KKTSolver:
 class KKTBatch:
     """Several bound KKTSolver handles refactored together (kkt_batch_*): one launch per
     dependency level across the batch, replayed from one HIP graph.  The solvers must stay
-    alive and bound while the batch is used."""
+    alive, bound and with the same schedule (not retuned) while the batch is used."""
 
     def __init__(self, solvers):
         self.solvers = list(solvers)

@@ -1449,8 +1449,9 @@ __device__ __forceinline__ void wide_item(const int item, const RefArgs<typename
 
 // ------------------------------------------------------------- wavefront path (medium items)
 
-// A medium item (every panel involved at most kMedW columns, the factored one at most kMedRows
-// rows) on one wavefront: no block barrier, the operands of the matrix-core updates loaded from
+// A medium item (every panel involved at most kMedW columns; no source has more than kWaveRows
+// rows below it and the factored panel no more than kWaveRows rows, by the schedule's choice of
+// the levels) on one wavefront: no block barrier, the operands of the matrix-core updates loaded from
 // the factor straight into their lanes, and a quarter of the 256-thread form's registers and LDS
 // per item, so that four times as many are in flight.  A group is one source and up to kWaveT
 // targets.  An update's products and sums are those of the wide path, in its order.
@@ -2216,10 +2217,6 @@ struct SolveLds {
 static_assert(offsetof(SolveLds, blk) % 16 == 0, "the staged panel is read in 16-byte pairs");
 static_assert(sizeof(SolveLds) <= kSolveLdsBytes, "LDS of the forward items in a refactorization launch");
 
-// kMulti: a.ncol right-hand sides in one launch, each item once per column, the columns of an
-// item on consecutive tickets.  The chain of levels, not the work, bounds a solve, so columns
-// beside each other cost little more than one (25,000 buses, two columns: 639 -> 398 us; each
-// column's result is the one it gets alone).
 constexpr int kPersThreads = kBlock + 64;   // threads of the persistent solves' blocks
 
 // the buffers of column c > 0
@@ -2237,6 +2234,10 @@ __device__ __forceinline__ void solve_item(const SolveArgs<TF> &a, int item, Sol
     else usolve_item<true>(a, item, L.ext, L.blk);
 }
 
+// kMulti: a.ncol right-hand sides in one launch, each item once per column, the columns of an
+// item on consecutive tickets.  The chain of levels, not the work, bounds a solve, so columns
+// beside each other cost little more than one (25,000 buses, two columns: 639 -> 398 us; each
+// column's result is the one it gets alone).
 template <bool kFwd, bool kMulti, class TF>
 __device__ __forceinline__ void persistent_items(int i0, int i1, const SolveArgs<TF> &a) {
     __shared__ SolveLds L;

@@ -45,7 +45,7 @@ constexpr int kFuseSolveBlocks = 256;
 // most copy blocks of a refactor launch per compute unit (1: 1.3% slower at 70k, 16: same)
 constexpr int kCopyBlocksPerCu = 4;
 constexpr int kDotBlocks = 512;
-constexpr int kNormRowBlocks = 4096;   // most blocks of the row-norm pass (8 lanes per row)
+constexpr int kNormRowBlocks = 4096;   // most blocks of the residual pass (8 lanes per 4 rows)
 // narrow items per level up to which the pipelined variant runs (a tiny item counts a quarter:
 // its 4-lane group keeps four times as many items in flight)
 constexpr int kSmallPipeMax = 100000;
@@ -101,10 +101,10 @@ struct kkt_handle {
     // (created at the first bind) and replayed on the caller's stream
     hipStream_t cap = nullptr;
     hipGraphExec_t levels = nullptr;
-    hipEvent_t levels_done = nullptr;   // recorded after every replay, on the caller's stream
+    hipEvent_t levels_done = nullptr;   // recorded after its every replay, on the caller's stream
     bool levels_failed = false;
-    // kkt_refactor_refine: the level launches with the forward solve riding in them,
-    // recorded at its first call
+    // kkt_refactor_refine: the launches of a whole step (enqueue_step), recorded at its first
+    // call; every call waits for its replay
     hipGraphExec_t fused = nullptr;
     bool fused_failed = false;
     // launch profiler
